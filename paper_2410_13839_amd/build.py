@@ -10,7 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmtp.so")
 PROBE_LIB = os.path.join(PKG, "libmtp_probe.so")
-SOURCES = ["api.hip", "gemm.hip", "gemv.hip", "attention.hip", "attn_mfma.hip", "rowops.hip", "select.hip", "qest.hip",
+SOURCES = ["api.hip", "gemm.hip", "f32.hip", "gemv.hip", "attention.hip", "attn_mfma.hip", "rowops.hip", "select.hip", "qest.hip",
            "qkv_attn.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

@@ -297,10 +297,9 @@ int hip_fail(mtp_ctx* c, hipError_t e, const char* where) {
 int pick_splits(const mtp_ctx* c, int M, int N, int K) {
     if (c->cfg.dtype != MTP_DTYPE_BF16) return 1;
     const int64_t cap_rows = std::max(c->ws.m_pre * 4, c->ws.m_dec * (int64_t)MTP_SPLITK_MAX);
-    const int gran = gemm_split_granule(1, M);
     const int tiles = gemm_tiles(M, N);
     int s = 1;
-    while (s < MTP_SPLITK_MAX && tiles * s < 256 && K % (gran * s * 2) == 0 && (int64_t)M * s * 2 <= cap_rows) s *= 2;
+    while (s < MTP_SPLITK_MAX && tiles * s < 256 && K % (32 * s * 2) == 0 && (int64_t)M * s * 2 <= cap_rows) s *= 2;
     return s;
 }
 
@@ -447,6 +446,36 @@ int run_layer_fused(mtp_ctx* c, int l, int rows, int qt) {
     return MTP_OK;
 }
 
+// One layer of the fp32 decode trunk for at most 16 rows: LayerNorm in the
+// products that read the residual rows, the residual added in the epilogues
+// of the two that write them.
+int run_layer_f32(mtp_ctx* c, int l, int rows, int qt) {
+    const mtp_config& cf = c->cfg;
+    const int d = cf.d_model, F = cf.d_ff;
+    float* h = c->ws_ptr<float>(c->ws.h);
+    GemmArgs g{};
+    g.epi = EPI_QKV; g.X = h; g.ldx = d; g.M = rows; g.W = c->lt(l, MTP_T_W_QKV); g.N = 3 * d; g.K = d;
+    g.xm = 1; g.ln_g = (const float*)c->lt(l, MTP_T_LN1_G); g.ln_b = (const float*)c->lt(l, MTP_T_LN1_B);
+    g.bias = (const float*)c->lt(l, MTP_T_B_QKV);
+    g.q = c->ws_ptr<float>(c->ws.q); g.rows = c->ws_ptr<RowInfo>(c->ws.rows); g.kv = c->kv(l); g.d = d;
+    HIPCHK(c, launch_rec(c, MTP_KCLASS_GEMM_QKV, [g](hipStream_t s) { return gemm(s, g); }), "qkv gemm");
+    HIPCHK(c, decode_attention(c, l, qt, true), "decode attention");
+    g = GemmArgs{};
+    g.epi = EPI_RESID; g.X = c->WS() + c->ws.attn; g.ldx = d; g.M = rows; g.W = c->lt(l, MTP_T_W_O); g.N = d; g.K = d;
+    g.bias = (const float*)c->lt(l, MTP_T_B_O); g.out = h; g.ldo = d;
+    HIPCHK(c, launch_rec(c, MTP_KCLASS_GEMM_OPROJ, [g](hipStream_t s) { return gemm(s, g); }), "out-proj gemm");
+    g = GemmArgs{};
+    g.epi = EPI_GELU; g.X = h; g.ldx = d; g.M = rows; g.W = c->lt(l, MTP_T_W_1); g.N = F; g.K = d;
+    g.xm = 1; g.ln_g = (const float*)c->lt(l, MTP_T_LN2_G); g.ln_b = (const float*)c->lt(l, MTP_T_LN2_B);
+    g.bias = (const float*)c->lt(l, MTP_T_B_1); g.out = c->WS() + c->ws.ffn; g.ldo = F;
+    HIPCHK(c, launch_rec(c, MTP_KCLASS_GEMM_FFN1, [g](hipStream_t s) { return gemm(s, g); }), "ffn1 gemm");
+    g = GemmArgs{};
+    g.epi = EPI_RESID; g.X = c->WS() + c->ws.ffn; g.ldx = F; g.M = rows; g.W = c->lt(l, MTP_T_W_2); g.N = d; g.K = F;
+    g.bias = (const float*)c->lt(l, MTP_T_B_2); g.out = h; g.ldo = d;
+    HIPCHK(c, launch_rec(c, MTP_KCLASS_GEMM_FFN2, [g](hipStream_t s) { return gemm(s, g); }), "ffn2 gemm");
+    return MTP_OK;
+}
+
 // One trunk layer over `rows` rows whose row/tile metadata is already on the device.
 int run_layer(mtp_ctx* c, int l, int rows, int n_tiles, int qt, int split_len, int n_splits, bool decode,
               bool bidir = false) {
@@ -581,8 +610,10 @@ int enqueue_step(mtp_ctx* c, int K, int top_k) {
         e.d = d; e.h = c->ws_ptr<float>(c->ws.h); e.u = c->WS() + c->ws.u;
         e.packed = dt == MTP_DTYPE_BF16 ? 1 : 0;   // fragment order, as in run_layer
         HIPCHK(c, embed_ln(st, e), "embed");
+        const bool f32_small = dt == MTP_DTYPE_F32 && gemm_f32_ln_ok(rows, d);
         for (int l = 0; l < cf.n_layers; ++l) {
-            int rc = run_layer(c, l, rows, B, qt, c->split_len, c->n_splits, true);
+            int rc = f32_small ? run_layer_f32(c, l, rows, qt)
+                               : run_layer(c, l, rows, B, qt, c->split_len, c->n_splits, true);
             if (rc) return rc;
         }
     }
@@ -598,6 +629,13 @@ int enqueue_step(mtp_ctx* c, int K, int top_k) {
         g.g = (const float*)c->wt(MTP_T_LNF_G); g.beta = (const float*)c->wt(MTP_T_LNF_B);
         g.bias = (const float*)c->wt(MTP_T_B_HEADS); g.out = c->WS() + c->ws.logits; g.ldo = K * V;
         HIPCHK(c, launch_rec(c, MTP_KCLASS_HEADS, [g](hipStream_t s) { return gemv(s, g); }), "heads gemv");
+    } else if (dt == MTP_DTYPE_F32 && gemm_f32_ln_ok(B, d)) {
+        GemmArgs g{};
+        g.epi = EPI_LOGITS; g.X = c->WS() + c->ws.h; g.ldx = d; g.M = B; g.W = c->wt(MTP_T_W_HEADS); g.N = K * V; g.K = d;
+        g.xm = 2; g.ln_g = (const float*)c->wt(MTP_T_LNF_G); g.ln_b = (const float*)c->wt(MTP_T_LNF_B);
+        g.st = c->ws_ptr<SeqState>(c->ws.state); g.Q = Q; g.hz = c->ws_ptr<float>(c->ws.hz);
+        g.bias = (const float*)c->wt(MTP_T_B_HEADS); g.out = c->WS() + c->ws.logits; g.ldo = K * V;
+        HIPCHK(c, launch_rec(c, MTP_KCLASS_HEADS, [g](hipStream_t s) { return gemm(s, g); }), "heads gemm");
     } else {
         FinalArgs f{};
         f.dtype = dt; f.B = B; f.d = d; f.mode = 0; f.Q = Q; f.st = c->ws_ptr<SeqState>(c->ws.state);
@@ -746,7 +784,9 @@ int plan_splits(mtp_ctx* c, int Q) {
         const int64_t bh = B * cf.n_heads;
         const int64_t want = std::max<int64_t>(1, (192 + bh - 1) / bh);
         sl = (max_ctx + want - 1) / want;
-        sl = std::max<int64_t>(64, (sl + 63) / 64 * 64);
+        // fp32: at least the 256 keys that attn_decode_kernel takes at once
+        // (shorter splits add the merge launch and save nothing)
+        sl = std::max<int64_t>(cf.dtype == MTP_DTYPE_F32 ? 256 : 64, (sl + 63) / 64 * 64);
     }
     if (const char* env = getenv("MTP_SPLIT_LEN")) {
         const int64_t v = atoll(env);

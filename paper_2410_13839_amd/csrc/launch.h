@@ -22,10 +22,15 @@ struct GemmArgs {
     const float* bias;
     void* out; int ldo; size_t split_stride;   // EPI_RESID: out = the fp32 residual stream
     float* q; const RowInfo* rows; KVView kv; int d;
+    // fp32 products of at most 16 rows (f32.hip): X = LayerNorm(X) in the
+    // kernel.  1: of the rows; 2: of each sequence's last pending row (M
+    // sequences of Q rows each, from st), copied to hz, or of hz when it has none
+    int xm; const float* ln_g; const float* ln_b; const SeqState* st; int Q; float* hz;
 };
 
 hipError_t gemm(hipStream_t st, const GemmArgs& a);
-int gemm_split_granule(int dtype, int M);
+hipError_t gemm_f32(hipStream_t st, const GemmArgs& a);
+bool gemm_f32_ln_ok(int M, int K);
 int gemm_tiles(int M, int N);
 int gemm_resid_in_place(int M, int N);
 
