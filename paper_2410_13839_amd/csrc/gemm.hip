@@ -12,8 +12,8 @@
 //    each wave loading its own activation fragments from L2 (no LDS staging:
 //    no two waves read the same k), and one LDS reduction over the waves
 //    precedes the epilogue.  The grid is sized so every CU streams.
-//  * gemm_big_bf16: M > 256 (prefill, NAR).  256 x 256 tiles on MFMA with
-//    both operands streamed global -> LDS in fragment order.
+//  * gemm_pp_bf16, gemm_duo_bf16: M > 256 (prefill, NAR).  Large tiles on
+//    MFMA with both operands streamed global -> LDS in fragment order.
 // The fp32 model's products are in f32.hip.
 #include <algorithm>
 #include <type_traits>
@@ -163,22 +163,21 @@ static void launch_med_x(hipStream_t st, const bf16_t* X, int ldx, int M, const 
 }
 
 // ---------------------------------------------------------------- large bf16
-// M > 256 (prefill, NAR).  Tiles of BM rows x BN columns (256 x 256 and
-// 256 x 128 with 8 waves in a 2 x 4 grid, each wave owning 128 x BN/4
-// outputs as 8 x BN/64 v_mfma_f32_16x16x32_bf16 tiles; 128 x 128 with 4
-// waves in a 2 x 2 grid, 64 x 64 outputs each, for products too small to
-// give the CUs enough of the larger tiles).  Both
-// operands are in fragment order (activations written so by their producers,
-// weights packed at load), so a 16 x 32 fragment is one contiguous 1 KB; it
-// travels global -> LDS by one global_load_lds_dwordx4 per wave (lane l's 16
-// bytes land at byte 16 l, the order the MFMA operand read wants: every
-// ds_read_b128 is conflict free) with no register staging.  K advances 32 per
-// stage through NS = 4 LDS stages, NS - 1 of them in flight while one is
-// consumed.  Each stage buffer is its own LDS object and the stage loop is
-// unrolled by NS, so the compiler's LDS-DMA waits see which buffer a read
-// touches.  Workgroups are numbered so that the ones sharing an XCD (the
-// dispatcher deals workgroups to the 8 XCDs in turn) take neighbouring tiles
-// of one row band, which they share through that XCD's L2.
+// Prefill, NAR (M > 256) and wide products of fewer rows: tiles of BM rows x
+// BN columns, 16 x 16 x 32 MFMA.  Both operands are in fragment order
+// (activations written so by their producers, weights packed at load), so a
+// 16 x 32 fragment is one contiguous 1 KB; it travels global -> LDS by one
+// global_load_lds_dwordx4 per wave (lane l's 16 bytes land at byte 16 l, the
+// order the MFMA operand read wants: every ds_read_b128 is conflict free) with
+// no register staging.  K advances 32 per stage through NS = 4 LDS stages, NS
+// - 1 of them in flight while one is consumed.  Workgroups are numbered so
+// that the ones sharing an XCD (the dispatcher deals workgroups to the 8 XCDs
+// in turn) take neighbouring tiles of one row band, which they share through
+// that XCD's L2.
+//
+// Two kernels: gemm_pp_bf16 (256 columns, eight waves in two groups that take
+// turns at LDS and the matrix cores) and gemm_duo_bf16 (128 columns, four
+// waves, two workgroups per CU).
 constexpr int GB_NS = 4;
 
 __device__ __forceinline__ constexpr int vmcnt_imm(int n) {
@@ -195,25 +194,131 @@ __device__ __forceinline__ void gb_barrier() {
     asm volatile("" ::: "memory");
 }
 
-template <int BM, int BN, int NWV, class Epi>
-__global__ __launch_bounds__(64 * NWV) void gemm_big_bf16(const bf16_t* __restrict__ X, int M,
-                                                          const bf16_t* __restrict__ W, int N, int K, int k_per_split,
-                                                          int tiles_m, int tiles_n, Epi epi) {
-    constexpr int FM = BM / 16, FN = BN / 16;   // 16-row fragments of a stage
-    constexpr int NF = FM + FN;                 // fragments per stage (one 32-k step)
-    constexpr int NL = NF / NWV;                // global_load_lds per wave per stage
-    constexpr int WGN = NWV / 2;                // waves along n (two along m)
-    constexpr int WFM = FM / 2, WFN = FN / WGN; // fragments per wave
-    static_assert(NF % NWV == 0 && (WFM == 8 || WFM == 4) && WFN >= 1, "tile shape");
-    typedef __attribute__((address_space(3))) void lds_void;
-    __shared__ __attribute__((aligned(1024))) bf16_t s0[NF * 512];
-    __shared__ __attribute__((aligned(1024))) bf16_t s1[NF * 512];
-    __shared__ __attribute__((aligned(1024))) bf16_t s2[NF * 512];
-    __shared__ __attribute__((aligned(1024))) bf16_t s3[NF * 512];
+// Outputs of a wave's WFN x WFM fragments, from activation fragment mf and
+// weight fragment nf on.
+template <int WFM, int WFN, class Epi>
+__device__ __forceinline__ void store_tile(const f32x4_t (&acc)[WFN][WFM], const Epi& epi, int mf, int nf, int M, int N,
+                                           int split, int r, int g) {
+    // epilogue: lane (r, g) of tile (i, j) holds outputs n = 4 g .. 4 g + 3
+    // of weight fragment i, row m = r of activation fragment j.  The
+    // rows' operands load once; each column fragment's operands load
+    // while the previous fragment's outputs are stored, so a wave does not
+    // wait a memory round trip per store.  A wave whose
+    // outputs all lie inside the product (and whose rows are all stored)
+    // stores without guards.
+    int em[WFM], emc[WFM];
+    typename Epi::RowKey rk[WFM];
+    typename Epi::RowPre rp[WFM];
+    bool rows_ok = true;
+#pragma unroll
+    for (int j = 0; j < WFM; ++j) {
+        em[j] = (mf + j) * 16 + r;
+        emc[j] = min(em[j], M - 1);
+        rk[j] = epi.row_key(emc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < WFM; ++j) rp[j] = epi.row(rk[j]);
+#pragma unroll
+    for (int j = 0; j < WFM; ++j) rows_ok = rows_ok && epi.ok(rp[j]);
+    const bool inside = (mf + WFM) * 16 <= M && (nf + WFN) * 16 <= N;   // uniform
+    const bool fast = inside && __all(rows_ok);
+    // column operands (biases) and per-output operands (the residual
+    // values) go out one fragment ahead of the stores; the latter in two sets
+    // of registers, which the operands of the product have left free (one set,
+    // a round trip per fragment: the 10678 x 1024 x 4096 product with the
+    // residual took 97 us, with two 87 us)
+    typename Epi::ColPre cp[2];
+    typename Epi::ElemPre ep[2][WFM];
+    auto col_n = [&](int i) {
+        const int n = (nf + i) * 16 + 4 * g;
+        return n < N ? n : ((N - 1) & ~3);
+    };
+    auto store_all = [&](auto guarded) {
+        constexpr bool GUARD = decltype(guarded)::value;
+        cp[0] = epi.col(col_n(0));
+#pragma unroll
+        for (int j = 0; j < WFM; ++j) ep[0][j] = epi.elem(emc[j], col_n(0));
+#pragma unroll
+        for (int i = 0; i < WFN; ++i) {
+            if (i + 1 < WFN) {
+                cp[(i + 1) & 1] = epi.col(col_n(i + 1));
+#pragma unroll
+                for (int j = 0; j < WFM; ++j) ep[(i + 1) & 1][j] = epi.elem(emc[j], col_n(i + 1));
+            }
+            const int n = (nf + i) * 16 + 4 * g;
+#pragma unroll
+            for (int j = 0; j < WFM; ++j) {
+                const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+                if (!GUARD) {
+                    epi.template store<true>(rp[j], cp[i & 1], ep[i & 1][j], em[j], n, v, split, 4);
+                } else if (em[j] < M && n < N) {
+                    epi.template store<false>(rp[j], cp[i & 1], ep[i & 1][j], em[j], n, v, split, min(4, N - n));
+                }
+            }
+        }
+    };
+    if (fast) store_all(std::false_type{});
+    else store_all(std::true_type{});
+}
 
+// The operand fragments of one 32-k step of a wave: 4 of the weights at LDS
+// byte address pa, WFM of the activations at pb, 1 KB each.  One asm block
+// issues the reads and waits for them: the compiler cannot tell the stage
+// being read from those the LDS DMA is filling, and would wait for them too.
+template <int WFM>
+__device__ __forceinline__ void pp_read(bf16x8_t (&a)[4], bf16x8_t (&b)[WFM], uint32_t pa, uint32_t pb) {
+    static_assert(WFM >= 4 && WFM <= 8, "row fragments per wave");
+#define PP_A                                                                                       \
+    "ds_read_b128 %0, %[pa] offset:0\n\tds_read_b128 %1, %[pa] offset:1024\n\t"                    \
+    "ds_read_b128 %2, %[pa] offset:2048\n\tds_read_b128 %3, %[pa] offset:3072\n\t"                 \
+    "ds_read_b128 %4, %[pb] offset:0\n\tds_read_b128 %5, %[pb] offset:1024\n\t"                    \
+    "ds_read_b128 %6, %[pb] offset:2048\n\tds_read_b128 %7, %[pb] offset:3072\n\t"
+#define PP_B4 "ds_read_b128 %8, %[pb] offset:4096\n\t"
+#define PP_B5 "ds_read_b128 %9, %[pb] offset:5120\n\t"
+#define PP_B6 "ds_read_b128 %10, %[pb] offset:6144\n\t"
+#define PP_B7 "ds_read_b128 %11, %[pb] offset:7168\n\t"
+#define PP_W "s_waitcnt lgkmcnt(0)"
+#define PP_O                                                                                                     \
+    "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
+#define PP_I [pa] "v"(pa), [pb] "v"(pb)
+    if constexpr (WFM == 4) asm volatile(PP_A PP_W : PP_O : PP_I : "memory");
+    else if constexpr (WFM == 5) asm volatile(PP_A PP_B4 PP_W : PP_O, "=&v"(b[4]) : PP_I : "memory");
+    else if constexpr (WFM == 6) asm volatile(PP_A PP_B4 PP_B5 PP_W : PP_O, "=&v"(b[4]), "=&v"(b[5]) : PP_I : "memory");
+    else if constexpr (WFM == 7)
+        asm volatile(PP_A PP_B4 PP_B5 PP_B6 PP_W : PP_O, "=&v"(b[4]), "=&v"(b[5]), "=&v"(b[6]) : PP_I : "memory");
+    else
+        asm volatile(PP_A PP_B4 PP_B5 PP_B6 PP_B7 PP_W
+                     : PP_O, "=&v"(b[4]), "=&v"(b[5]), "=&v"(b[6]), "=&v"(b[7]) : PP_I : "memory");
+#undef PP_A
+#undef PP_B4
+#undef PP_B5
+#undef PP_B6
+#undef PP_B7
+#undef PP_W
+#undef PP_O
+#undef PP_I
+}
+
+// Tiles of BM = 32 WFM rows x 128 columns, four waves in a 2 x 2 grid, two
+// workgroups per CU (at most 80 KB of stages each): nothing keeps the two in
+// step, so one multiplies while the other reads its operands, starts or stores
+// a tile.  That makes it the kernel for products whose epilogue moves more
+// than their operands (the residual read and written, few tiles per CU): 10678
+// x 1024 x 4096 with the residual 85.9 us (192 rows) against 87.4 with
+// gemm_pp_bf16, 6720 x 1024 x 4096 63.9 (128 rows) against 68.7; and, with 128
+// rows, for products of few tiles.
+template <int WFM, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict__ X, int M, const bf16_t* __restrict__ W,
+                                                    int N, int K, int k_per_split, int tiles_m, int tiles_n, Epi epi) {
+    constexpr int NWV = 4, WFN = 4;
+    constexpr int FM = 2 * WFM, FN = 2 * WFN;   // 16-row fragments of a stage (one 32-k step)
+    constexpr int NF = FM + FN;
+    constexpr int NS = NF <= 20 ? 4 : 3;        // stages: at most 80 KB
+    constexpr int NL = (NF + NWV - 1) / NWV;    // global_load_lds per wave per stage (the last ones may repeat)
+    __shared__ __attribute__((aligned(1024))) bf16_t stage[NS * NF * 512];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / WGN, wn = wave - wm * WGN;
+    const int wm = wave >> 1, wn = wave & 1;
     // tiles of this workgroup: XCD x (= bid % 8) takes the x-th eighth of the
     // tiles in row-band order (n fastest), and its workgroups take them in
     // turn (workgroup j of the XCD: tiles j, j + wgx, ...), so the ones in
@@ -230,276 +335,334 @@ __global__ __launch_bounds__(64 * NWV) void gemm_big_bf16(const bf16_t* __restri
     const int ks0 = (split * k_per_split) >> 5; // first 32-k step
     const int nst = k_per_split >> 5;
     const int K32 = K >> 5;
-
-    // fragment f of a stage: f < FM is activation rows 16 f.., else weight
-    // rows 16 (f - FM)..; wave w issues f = w, w + NWV, ...
-    int mfr0 = 0, nfr0 = 0;                     // first 16-row fragment of each operand
+    const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)stage + lane * 16;
+    const int r = lane & 15, g = lane >> 4;
+    int mfr0 = 0, nfr0 = 0;
     const bf16_t* src[NL];
+    int dst[NL];
     auto set_tile = [&](int tt) {
         const int tm = tt / tiles_n, tn = tt - tm * tiles_n;
         mfr0 = tm * FM;
         nfr0 = tn * FN;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int f = wave + NWV * i;
-            const bf16_t* base;
-            if (f < FM) base = X + (size_t)min(mfr0 + f, mfr_last) * K32 * 512;
-            else base = W + (size_t)min(nfr0 + f - FM, nfr_last) * K32 * 512;
-            src[i] = base + (size_t)ks0 * 512 + lane * 8;
+            const int f = min(wave + NWV * i, NF - 1);
+            const bf16_t* b;
+            if (f < FM) b = X + (size_t)min(mfr0 + f, mfr_last) * K32 * 512;
+            else b = W + (size_t)min(nfr0 + f - FM, nfr_last) * K32 * 512;
+            src[i] = b + (size_t)ks0 * 512 + lane * 8;
+            dst[i] = f * 512;
         }
     };
-    set_tile(t);
-    auto issue = [&](bf16_t* buf, int st) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto issue = [&](int st, int bi) {
+        bf16_t* buf = stage + bi * (NF * 512);
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)st * 512),
-                                             (lds_void*)(buf + (wave + NWV * i) * 512), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)st * 512), (lds_void*)(buf + dst[i]), 16, 0, 0);
     };
-
-    f32x4_t acc[WFN][WFM];
+    auto issue_first = [&]() {
 #pragma unroll
-    for (int i = 0; i < WFN; ++i)
-#pragma unroll
-        for (int j = 0; j < WFM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // Operand reads are ds_read_b128 in asm: the compiler cannot tell the
-    // stage being read from the stages the LDS DMA is still filling and would
-    // wait for every load in flight before each read.  The stage read is
-    // complete (the vmcnt wait and barrier before it).  Each asm block issues
-    // its reads and waits for them itself, so its outputs are valid when it
-    // ends whatever the compiler does with the registers afterwards.
-    auto compute = [&](const bf16_t* buf) {
-        const uint32_t lb = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)buf + lane * 16;
-        const uint32_t la = lb + (FM + wn * WFN) * 1024, lbm = lb + wm * WFM * 1024;
-        bf16x8_t a[WFN], b[WFM];
-        static_assert((WFN == 8 || WFN == 4 || WFN == 2), "operand counts");
-        if constexpr (WFN == 8) {
-            asm volatile(
-                "ds_read_b128 %0, %8 offset:0\n\tds_read_b128 %1, %8 offset:1024\n\t"
-                "ds_read_b128 %2, %8 offset:2048\n\tds_read_b128 %3, %8 offset:3072\n\t"
-                "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %8 offset:5120\n\t"
-                "ds_read_b128 %6, %8 offset:6144\n\tds_read_b128 %7, %8 offset:7168\n\t"
-                "s_waitcnt lgkmcnt(0)"
-                : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]), "=&v"(a[6]),
-                  "=&v"(a[7])
-                : "v"(la)
-                : "memory");
-        } else if constexpr (WFN == 4) {
-            asm volatile(
-                "ds_read_b128 %0, %4 offset:0\n\tds_read_b128 %1, %4 offset:1024\n\t"
-                "ds_read_b128 %2, %4 offset:2048\n\tds_read_b128 %3, %4 offset:3072\n\t"
-                "s_waitcnt lgkmcnt(0)"
-                : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
-                : "v"(la)
-                : "memory");
-        } else {
-            asm volatile(
-                "ds_read_b128 %0, %2 offset:0\n\tds_read_b128 %1, %2 offset:1024\n\t"
-                "s_waitcnt lgkmcnt(0)"
-                : "=&v"(a[0]), "=&v"(a[1])
-                : "v"(la)
-                : "memory");
-        }
-        if constexpr (WFM == 8) {
-            asm volatile(
-                "ds_read_b128 %0, %8 offset:0\n\tds_read_b128 %1, %8 offset:1024\n\t"
-                "ds_read_b128 %2, %8 offset:2048\n\tds_read_b128 %3, %8 offset:3072\n\t"
-                "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %8 offset:5120\n\t"
-                "ds_read_b128 %6, %8 offset:6144\n\tds_read_b128 %7, %8 offset:7168\n\t"
-                "s_waitcnt lgkmcnt(0)"
-                : "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3]), "=&v"(b[4]), "=&v"(b[5]), "=&v"(b[6]),
-                  "=&v"(b[7])
-                : "v"(lbm)
-                : "memory");
-        } else {
-            asm volatile(
-                "ds_read_b128 %0, %4 offset:0\n\tds_read_b128 %1, %4 offset:1024\n\t"
-                "ds_read_b128 %2, %4 offset:2048\n\tds_read_b128 %3, %4 offset:3072\n\t"
-                "s_waitcnt lgkmcnt(0)"
-                : "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
-                : "v"(lbm)
-                : "memory");
-        }
-#pragma unroll
-        for (int i = 0; i < WFN; ++i)
-#pragma unroll
-            for (int j = 0; j < WFM; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int s = 0; s < NS - 1; ++s)
+            if (s < nst) issue(s, s);
     };
-
-    // prologue: stages 0 .. NS-2 in flight
-    if (0 < nst) issue(s0, 0);
-    if (1 < nst) issue(s1, 1);
-    if (2 < nst) issue(s2, 2);
-    const int r = lane & 15, g = lane >> 4;
-    for (bool later = false;; later = true) {
-        // step st: wait for stage st (the NS-2 later stages may stay in
-        // flight; on a later tile the first step waits for everything, the
-        // previous tile's output stores included), barrier (stage st visible
-        // to all waves, and every wave is done with the buffer stage st +
-        // NS - 1 refills), refill, consume
-#define GB_STEP(BUF, NEXT, U)                                                          \
-        {                                                                              \
-            const int st = st0 + (U);                                                  \
-            if (st < nst) {                                                            \
-                if (later && st == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));        \
-                else if (st + 2 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));  \
-                else if (st + 1 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));      \
-                else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                         \
-                gb_barrier();                                                          \
-                if (st + GB_NS - 1 < nst) issue(NEXT, st + GB_NS - 1);                 \
-                compute(BUF);                                                          \
-            }                                                                          \
-        }
-        for (int st0 = 0; st0 < nst; st0 += GB_NS) {
-            GB_STEP(s0, s3, 0)
-            GB_STEP(s1, s0, 1)
-            GB_STEP(s2, s1, 2)
-            GB_STEP(s3, s2, 3)
-        }
-#undef GB_STEP
-        // the next tile's first stages go out before this tile's outputs are
-        // stored, once every wave is done reading the stage buffers
-        const int em0 = mfr0, en0 = nfr0;
-        const int t_next = t + wgx;
-        const bool more = t_next < t_end;      // uniform
-        if (more) {
-            gb_barrier();
-            set_tile(t_next);
-            if (0 < nst) issue(s0, 0);
-            if (1 < nst) issue(s1, 1);
-            if (2 < nst) issue(s2, 2);
-        }
-        // epilogue: lane (r, g) of tile (i, j) holds outputs n = 4 g .. 4 g + 3
-        // of weight fragment i, row m = r of activation fragment j.  The
-        // rows' operands load once; each column fragment's operands load
-        // while the previous fragment's outputs are stored, so a wave waits
-        // about WFN + 1 memory round trips, not one per store.  A wave whose
-        // outputs all lie inside the product (and whose rows are all stored)
-        // stores without guards.
-        int em[WFM], emc[WFM];
-        typename Epi::RowKey rk[WFM];
-        typename Epi::RowPre rp[WFM];
-        bool rows_ok = true;
-#pragma unroll
-        for (int j = 0; j < WFM; ++j) {
-            em[j] = (em0 + wm * WFM + j) * 16 + r;
-            emc[j] = min(em[j], M - 1);
-            rk[j] = epi.row_key(emc[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < WFM; ++j) rp[j] = epi.row(rk[j]);
-#pragma unroll
-        for (int j = 0; j < WFM; ++j) rows_ok = rows_ok && epi.ok(rp[j]);
-        const bool inside = (em0 + wm * WFM + WFM) * 16 <= M && (en0 + wn * WFN + WFN) * 16 <= N;   // uniform
-        const bool fast = inside && __all(rows_ok);
-        // column operands (biases) go out one fragment ahead; per-output
-        // operands (the residual values) one fragment at a time, after the
-        // previous fragment's stores, for want of registers (the 128 of the
-        // accumulators are still live)
-        typename Epi::ColPre cp[2];
-        typename Epi::ElemPre ep[WFM];
-        auto col_n = [&](int i) {
-            const int n = (en0 + wn * WFN + i) * 16 + 4 * g;
-            return n < N ? n : ((N - 1) & ~3);
-        };
-        auto store_all = [&](auto guarded) {
-            constexpr bool GUARD = decltype(guarded)::value;
-            cp[0] = epi.col(col_n(0));
-#pragma unroll
-            for (int j = 0; j < WFM; ++j) ep[j] = epi.elem(emc[j], col_n(0));
-#pragma unroll
-            for (int i = 0; i < WFN; ++i) {
-                if (i + 1 < WFN) cp[(i + 1) & 1] = epi.col(col_n(i + 1));
-                const int n = (en0 + wn * WFN + i) * 16 + 4 * g;
-#pragma unroll
-                for (int j = 0; j < WFM; ++j) {
-                    const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-                    if (!GUARD) {
-                        epi.template store<true>(rp[j], cp[i & 1], ep[j], em[j], n, v, split, 4);
-                    } else if (em[j] < M && n < N) {
-                        epi.template store<false>(rp[j], cp[i & 1], ep[j], em[j], n, v, split, min(4, N - n));
-                    }
-                }
-                if (i + 1 < WFN) {
-#pragma unroll
-                    for (int j = 0; j < WFM; ++j) ep[j] = epi.elem(emc[j], col_n(i + 1));
-                }
-            }
-        };
-        if (fast) store_all(std::false_type{});
-        else store_all(std::true_type{});
+    set_tile(t);
+    issue_first();
+    bool later = false;
+    while (true) {
+        f32x4_t acc[WFN][WFM];
 #pragma unroll
         for (int i = 0; i < WFN; ++i)
 #pragma unroll
             for (int j = 0; j < WFM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        int bi = 0;
+        for (int st = 0; st < nst; ++st) {
+            // wait for stage st (the later ones may stay in flight; on a later
+            // tile the first step waits for everything, the previous tile's
+            // output stores included), barrier (stage st visible to all waves,
+            // and every wave is done with the buffer that the next issue
+            // refills), refill, consume
+            if (later && st == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            else if (NS == 4 && st + 2 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));
+            else if (st + 1 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            gb_barrier();
+            const int bn = bi == 0 ? NS - 1 : bi - 1;
+            if (st + NS - 1 < nst) issue(st + NS - 1, bn);
+            const uint32_t lb = base + bi * (NF * 1024);
+            bf16x8_t a[WFN], b[WFM];
+            pp_read<WFM>(a, b, lb + (FM + wn * WFN) * 1024, lb + wm * WFM * 1024);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < WFN; ++i)
+#pragma unroll
+                for (int j = 0; j < WFM; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            bi = bi + 1 == NS ? 0 : bi + 1;
+        }
+        // the next tile's first stages go out before this tile's outputs are
+        // stored, once every wave is done reading the stage buffers
+        gb_barrier();
+        const int em0 = mfr0 + wm * WFM, en0 = nfr0 + wn * WFN;
+        t += wgx;
+        const bool more = t < t_end;            // uniform
+        if (more) {
+            set_tile(t);
+            issue_first();
+        }
+        store_tile<WFM, WFN>(acc, epi, em0, en0, M, N, split, r, g);
         if (!more) break;
-        t = t_next;
+        later = true;
     }
 }
 
-template <int BM, int BN, int NWV, class Epi>
-static hipError_t launch_big(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, int N, int K, int splits,
-                             Epi epi) {
-    const int kps = K / splits;
-    if (kps % 32) return hipErrorInvalidValue;
-    const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-    const int ntile = tm * tn;
-    // the tile numbering deals eighths of the tiles to the XCDs; each XCD
-    // gets at most as many workgroups as it holds at once (its CUs times the
-    // workgroups per CU the LDS stages allow), and those take its tiles in
-    // turn, so a workgroup's next tile streams in while it stores the last
-    static int n_cu = 0;
-    if (n_cu == 0) {
+// M > 256, eight waves, tiles of BM = 32 WFM rows x 256 columns (WFM = 4 .. 8,
+// so that a product's tiles fill whole rounds of the CUs; see pick_tile).
+//
+// What bounds a tile of this size is LDS bandwidth against the matrix cores:
+// a 32-k step of 256 x 256 reads 96 KB of operands from LDS and lets 32 KB of
+// DMA in (1024 clocks at 128 bytes a clock) while its MFMAs take 1024 clocks
+// a SIMD, so the two have to run beside each other all the time.  With all
+// waves in step (read, then multiply, a barrier per stage) they take turns,
+// and the matrix cores were busy 56% of the time.  Here the two row groups of
+// four waves (one wave of each on every SIMD) run one barrier apart: while
+// one group reads its operands and asks for a later stage, the other
+// multiplies, with the higher wave priority.  Measured, fp32 output, against
+// the same tile in step: 10678 x 3072 x 1024 78.6 -> 69.7 us (964 TFLOP/s),
+// 10678 x 1024 x 4096 106.8 -> 78.9 us, 73.9 us with 192-row tiles (1.21
+// PFLOP/s).  Weights straight from global memory into registers instead of
+// LDS, a column-major tile order and a start in K of its own for each
+// workgroup all measured the same within 2%, or slower.
+//
+// A stage is landed for everyone once every wave has waited for its own DMA
+// of it and a barrier has passed: each wave waits at the end of the phase in
+// which it reads the stage before, one barrier ahead of the first reader.  A
+// buffer is refilled (stage st + 3 into that of st - 1) by a group that is
+// reading stage st; the other group is then multiplying st - 1 or later and
+// has read it.
+template <int WFM, class Epi>
+__global__ __launch_bounds__(512) void gemm_pp_bf16(const bf16_t* __restrict__ X, int M, const bf16_t* __restrict__ W,
+                                                    int N, int K, int k_per_split, int tiles_m, int tiles_n, Epi epi) {
+    constexpr int NWV = 8, WFN = 4;
+    constexpr int FM = 2 * WFM, FN = 4 * WFN;   // 16-row fragments of a stage (one 32-k step)
+    constexpr int NF = FM + FN;
+    constexpr int NL = (NF + NWV - 1) / NWV;    // global_load_lds per wave per stage (the last ones may repeat)
+    __shared__ __attribute__((aligned(1024))) bf16_t stage[GB_NS * NF * 512];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;    // wm: the group
+    // tiles of this workgroup, as in gemm_duo_bf16
+    const int ntile = tiles_m * tiles_n;
+    const int bid = blockIdx.x;
+    const int per = (ntile + 7) >> 3;
+    const int wgx = gridDim.x >> 3;
+    const int t_end = min(((bid & 7) + 1) * per, ntile);
+    int t = (bid & 7) * per + (bid >> 3);
+    if (t >= t_end) return;                     // uniform: whole workgroup
+    const int mfr_last = ((M + 15) >> 4) - 1, nfr_last = ((N + 15) >> 4) - 1;
+    const int split = blockIdx.y;
+    const int ks0 = (split * k_per_split) >> 5;
+    const int nst = k_per_split >> 5;
+    const int K32 = K >> 5;
+    const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)stage + lane * 16;
+    const int r = lane & 15, g = lane >> 4;
+
+    int mfr0 = 0, nfr0 = 0;
+    const bf16_t* src[NL];
+    int dst[NL];
+    auto set_tile = [&](int tt) {
+        const int tm = tt / tiles_n, tn = tt - tm * tiles_n;
+        mfr0 = tm * FM;
+        nfr0 = tn * FN;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int f = min(wave + NWV * i, NF - 1);
+            const bf16_t* b;
+            if (f < FM) b = X + (size_t)min(mfr0 + f, mfr_last) * K32 * 512;
+            else b = W + (size_t)min(nfr0 + f - FM, nfr_last) * K32 * 512;
+            src[i] = b + (size_t)ks0 * 512 + lane * 8;
+            dst[i] = f * 512;
+        }
+    };
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto issue = [&](int st) {
+        bf16_t* buf = stage + (st % GB_NS) * (NF * 512);
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)st * 512), (lds_void*)(buf + dst[i]), 16, 0, 0);
+    };
+    // the wait for this wave's part of the first stage: with the two later
+    // stages in flight, or for everything
+    auto issue_first = [&]() {
+#pragma unroll
+        for (int s = 0; s < GB_NS - 1; ++s)
+            if (s < nst) issue(s);
+    };
+    set_tile(t);
+    issue_first();
+    bool later = false;
+    while (true) {
+        f32x4_t acc[WFN][WFM];
+#pragma unroll
+        for (int i = 0; i < WFN; ++i)
+#pragma unroll
+            for (int j = 0; j < WFM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // (on a later tile the previous one's output stores are in the count)
+        if (!later && nst >= GB_NS - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm((GB_NS - 2) * NL));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        gb_barrier();
+        if (wm == 1) gb_barrier();              // the second group runs one barrier behind
+        for (int st = 0; st < nst; ++st) {
+            // reading phase
+            const uint32_t lb = base + (st % GB_NS) * (NF * 1024);
+            bf16x8_t a[WFN], b[WFM];
+            if (st + GB_NS - 1 < nst) issue(st + GB_NS - 1);
+            pp_read<WFM>(a, b, lb + (FM + wn * WFN) * 1024, lb + wm * WFM * 1024);
+            if (st + 3 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));
+            else if (st + 2 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            gb_barrier();
+            // multiplying phase
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < WFN; ++i)
+#pragma unroll
+                for (int j = 0; j < WFM; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            gb_barrier();
+        }
+        if (wm == 0) gb_barrier();              // every wave is past its last read here
+        // the next tile's first stages go out before this tile's outputs are stored
+        const int em0 = mfr0 + wm * WFM, en0 = nfr0 + wn * WFN;
+        t += wgx;
+        const bool more = t < t_end;            // uniform
+        if (more) {
+            set_tile(t);
+            issue_first();
+        }
+        store_tile<WFM, WFN>(acc, epi, em0, en0, M, N, split, r, g);
+        if (!more) break;
+        later = true;
+    }
+}
+
+// Compute units of the current device (256 where that cannot be asked).
+static int cu_count() {
+    static const int n = [] {
         int dev = 0, v = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8)
             v = 256;
-        n_cu = v;
-    }
-    constexpr int lds_kb = GB_NS * (BM / 16 + BN / 16);   // 1 KB per fragment per stage
-    const int per_cu = lds_kb <= 80 ? 2 : 1;               // 160 KB of LDS per CU
-    const int per_xcd = std::min((ntile + 7) / 8, std::max(1, n_cu / 8) * per_cu);
-    dim3 grid(8 * per_xcd, splits);
-    hipLaunchKernelGGL((gemm_big_bf16<BM, BN, NWV, Epi>), grid, dim3(64 * NWV), 0, st, X, M, W, N, K, kps, tm, tn, epi);
+        return v;
+    }();
+    return n;
+}
+
+// The tile numbering deals eighths of the tiles to the XCDs; each XCD gets at
+// most as many workgroups as it holds at once (its CUs times the workgroups
+// per CU that the LDS stages allow), and those take its tiles in turn, so a
+// workgroup's next tile streams in while it stores the last.
+template <int WFM, class Epi>
+static hipError_t launch_duo(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, int N, int K, int splits,
+                             Epi epi) {
+    const int kps = K / splits;
+    if (kps % 32) return hipErrorInvalidValue;
+    const int tm = (M + 32 * WFM - 1) / (32 * WFM), tn = (N + 127) / 128;
+    const int per_xcd = std::min((tm * tn + 7) / 8, cu_count() / 8 * 2);      // two per CU
+    hipLaunchKernelGGL((gemm_duo_bf16<WFM, Epi>), dim3(8 * per_xcd, splits), dim3(256), 0, st, X, M, W, N, K, kps, tm,
+                       tn, epi);
+    return hipGetLastError();
+}
+template <int WFM, class Epi>
+static hipError_t launch_pp(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, int N, int K, int splits,
+                            Epi epi) {
+    const int kps = K / splits;
+    if (kps % 32) return hipErrorInvalidValue;
+    const int tm = (M + 32 * WFM - 1) / (32 * WFM), tn = (N + 255) / 256;
+    const int per_xcd = std::min((tm * tn + 7) / 8, cu_count() / 8);
+    hipLaunchKernelGGL((gemm_pp_bf16<WFM, Epi>), dim3(8 * per_xcd, splits), dim3(512), 0, st, X, M, W, N, K, kps, tm, tn,
+                       epi);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ launchers
-// Tile of the large-M kernel for an M x N product (M > 256): 256 x 256 when
-// that gives at least 128 tiles (half the CUs), 256 x 128 when that gives
-// 192, else 128 x 128 when that gives 96 (64 for a split-K product, whose
-// K splits multiply the workgroups), else 256 x 128 when that gives 64;
-// otherwise {0, 0}: the product is too small for any and goes to the medium
-// kernel (64-row groups, one workgroup per 32 columns).  Measured at M =
-// 325 and 1,075: 72-81 tiles of 128 x 128 without K splits lose to the
-// medium kernel, 96 and more win against it and against 256 x 128.
-struct BigTile { int bm, bn; };
+// Tile of an M x N product.  rows: of the eight-wave kernel's
+// tiles (x 256 columns) when wide, of the four-wave kernel's (x 128 columns)
+// otherwise, 0 for the medium kernel (64-row groups, one workgroup per 32 columns).
+//
+// The eight-wave kernel needs one CU a tile and costs about as much for a
+// tile of 128 rows on a few CUs as on all: with fewer than 192 tiles of 128 x
+// 256 (three quarters of the CUs) the four-wave kernel's 128 x 128 tiles are
+// faster (weights cold: 1075 x 4096 x 1024, 144 against 288 tiles, 26.7
+// against 25.1 us; from 6720 rows and 1024 columns on, 212 tiles, the larger
+// ones win).  The row count is the one with the least rounds x rows: the
+// workgroups take tiles in rounds, and a last round costs as much as a full
+// one (6720 x 3072 x 1024, 27 x 12 tiles of 256 rows, 1.27 rounds: 59.9 us; 42
+// x 12 of 160, 1.97 rounds: 50.9 us; 10678 x 1024 x 4096, one round either
+// way: 256 rows 78.9, 192 rows 73.9 us).  32 rows are added for what a round
+// costs whatever its tiles.
+//
+// 128 x 128 when that gives 96 tiles (64 for a split-K product, whose K splits
+// multiply the workgroups).  Measured at M = 325 and 1,075: 72-81 of them
+// without K splits lose to the medium kernel, 96 and more win against it.
+struct BigTile { int rows; bool wide; };
 static int tile_count(int M, int N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
-static BigTile big_tile(int M, int N, bool splittable) {
-    if (tile_count(M, N, 256, 256) >= 128) return {256, 256};
-    if (tile_count(M, N, 256, 128) >= 192) return {256, 128};
-    if (tile_count(M, N, 128, 128) >= (splittable ? 64 : 96)) return {128, 128};
-    if (tile_count(M, N, 256, 128) >= 64) return {256, 128};
-    return {0, 0};
+// The row count with the least rounds x (rows + 32) over `slots` workgroups.
+static int best_rows(int M, int N, int bn, int slots, int most) {
+    int best = 0, best_cost = 0;
+    for (int bm = most; bm >= 128; bm -= 32) {
+        const int cost = (tile_count(M, N, bm, bn) + slots - 1) / slots * (bm + 32);
+        if (best == 0 || cost < best_cost) {
+            best = bm;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+static BigTile pick_tile(int M, int N, bool splittable, bool resid) {
+    if (tile_count(M, N, 128, 256) >= 192) {
+        // (the residual epilogue's operands leave no registers for 256 rows)
+        if (resid) return {best_rows(M, N, 128, 2 * cu_count(), 224), false};
+        return {best_rows(M, N, 256, cu_count(), 256), true};
+    }
+    if (tile_count(M, N, 128, 128) >= (splittable ? 64 : 96)) return {128, false};
+    return {0, false};
 }
 template <class Epi>
 static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K,
                               int splits, int xpk, Epi epi) {
+    constexpr bool resid = std::is_same<Epi, EpiResid>::value;
     if (splits < 1 || K % (32 * splits)) return hipErrorInvalidValue;
     if (M <= 16) {
         launch_med_x<1>(st, X, ldx, M, W, N, K, splits, xpk, epi);
     } else if (M <= 32) {
         launch_med_x<2>(st, X, ldx, M, W, N, K, splits, xpk, epi);
     } else {
-        const BigTile bt = big_tile(M, N, std::is_same<Epi, EpiPartial>::value);
-        if (bt.bm == 0) {
+        const BigTile bt = pick_tile(M, N, std::is_same<Epi, EpiPartial>::value, resid);
+        if (bt.rows == 0) {
             launch_med_x<4>(st, X, ldx, M, W, N, K, splits, xpk, epi);
+        } else if (!xpk) {
+            return hipErrorInvalidValue;   // large products take fragment-order activations only
+        } else if constexpr (resid) {
+            switch (bt.rows) {
+            case 128: return launch_duo<4>(st, X, M, W, N, K, splits, epi);
+            case 160: return launch_duo<5>(st, X, M, W, N, K, splits, epi);
+            case 192: return launch_duo<6>(st, X, M, W, N, K, splits, epi);
+            default: return launch_duo<7>(st, X, M, W, N, K, splits, epi);
+            }
         } else {
-            if (!xpk) return hipErrorInvalidValue;   // large products take fragment-order activations only
-            if (bt.bm == 128) return launch_big<128, 128, 4>(st, X, M, W, N, K, splits, epi);
-            return bt.bn == 256 ? launch_big<256, 256, 8>(st, X, M, W, N, K, splits, epi)
-                                : launch_big<256, 128, 8>(st, X, M, W, N, K, splits, epi);
+            if (!bt.wide) return launch_duo<4>(st, X, M, W, N, K, splits, epi);
+            switch (bt.rows) {
+            case 128: return launch_pp<4>(st, X, M, W, N, K, splits, epi);
+            case 160: return launch_pp<5>(st, X, M, W, N, K, splits, epi);
+            case 192: return launch_pp<6>(st, X, M, W, N, K, splits, epi);
+            case 224: return launch_pp<7>(st, X, M, W, N, K, splits, epi);
+            default: return launch_pp<8>(st, X, M, W, N, K, splits, epi);
+            }
         }
     }
     return hipGetLastError();
@@ -509,7 +672,7 @@ static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, c
 // NAR trunk), where a residual projection updates the residual stream in its
 // epilogue (EPI_RESID) instead of writing split-K partial sums.
 int gemm_resid_in_place(int M, int N) {
-    return M > 256 && big_tile(M, N, false).bm != 0;
+    return M > 256 && pick_tile(M, N, false, true).rows != 0;
 }
 
 // Workgroups of one split-K-able (partial-sum) bf16 launch for M rows and N
@@ -517,9 +680,9 @@ int gemm_resid_in_place(int M, int N) {
 int gemm_tiles(int M, int N) {
     const int groups = ((N + 15) / 16 + GM_NT - 1) / GM_NT;
     if (M <= 32) return groups;
-    const BigTile bt = M <= 256 ? BigTile{0, 0} : big_tile(M, N, true);
-    if (bt.bm == 0) return groups * ((M + 63) / 64);
-    return tile_count(M, N, bt.bm, bt.bn);
+    const BigTile bt = M <= 256 ? BigTile{0, false} : pick_tile(M, N, true, false);
+    if (bt.rows == 0) return groups * ((M + 63) / 64);
+    return tile_count(M, N, bt.rows, bt.wide ? 256 : 128);
 }
 
 hipError_t gemm(hipStream_t st, const GemmArgs& a) {

@@ -1,0 +1,56 @@
+"""The large-M products at the edges of their tiles: NAR modules whose row
+counts take each tile height of the eight-wave kernel (128 .. 256 rows), both
+kernels' ragged last tiles, and the first row counts past the medium kernel.
+Every row of every utterance is a target, so the stage logits show each output
+row; against the float64 oracle within the bf16 tolerance of test_gpu_nar.py
+(two layers: 3e-2 is twice what twelve show)."""
+import numpy as np
+import pytest
+
+from gpu_common import log
+from oracle.nar import NARModel
+from paper_2410_13839_amd.workloads import ModelShape, NarWorkload, make_nar_inputs, make_weights
+
+pytestmark = pytest.mark.gpu
+
+# rows -> the tile heights of the products of 3072 (QKV), 4096 (FFN1) and 1024
+# columns (residual), d 1024 over 256 CUs
+ROWS = {
+    257: "medium kernel, 128 (four waves), split K",
+    1536: "128 (four waves), 128 (eight waves), 128: the residual in the epilogue from here on",
+    2049: "128, 160 (one row in the last tile), 128",
+    2720: "160, 192, 128",
+    4001: "192, 256, 128",
+    4090: "224, 256, 128",
+    8209: "224, 192, 160",
+    10250: "256, 224, 192",
+}
+
+
+@pytest.mark.parametrize("rows", list(ROWS))
+def test_every_row_of_a_tiled_product(rows):
+    shape = ModelShape(n_layers=2, d_model=1024, n_heads=16, d_ff=4096, k_heads=1, dtype="bf16", vocab=257, eos_id=256,
+                       n_phone=8, max_pos=160, nar=True)
+    # utterances of 97 rows (odd starts in the tiles) and a rest
+    n, rest = divmod(rows, 97)
+    lens = [97] * n + ([rest] if rest else [])
+    wl = NarWorkload("tiles", shape, batch=len(lens), phon_len=(0, 0), prompt_len=(0, 0), target_len=(1, 97))
+    w = make_weights(shape, seed=43)
+    inp = make_nar_inputs(wl, seed_base=900)
+    rng = np.random.default_rng(rows)
+    inp.a1 = [rng.integers(0, shape.codebook, size=t).astype(np.int32) for t in lens]
+    from paper_2410_13839_amd.binding import NarSession
+    s = NarSession(shape, w, max_batch=len(lens), max_seq=97)
+    s.prepare(inp.phon, inp.prompt, inp.a1)
+    s.run()
+    got = s.logits(0)
+    s.close()
+    m = NARModel(shape, w)
+    worst, o = 0.0, 0
+    for b, t in enumerate(lens):
+        h = m.forward(m.embed(2, inp.phon[b], inp.prompt[b], inp.a1[b][None]))
+        err = float(np.max(np.abs(got[o:o + t] - m.stage_logits(h, 2))))
+        worst = max(worst, err)
+        assert err < 3e-2, (rows, b, err)
+        o += t
+    log(f"{rows} rows: max |logit err| {worst:.3g}")
