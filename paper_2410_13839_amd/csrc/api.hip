@@ -297,10 +297,8 @@ int hip_fail(mtp_ctx* c, hipError_t e, const char* where) {
 int pick_splits(const mtp_ctx* c, int M, int N, int K) {
     if (c->cfg.dtype != MTP_DTYPE_BF16) return 1;
     const int64_t cap_rows = std::max(c->ws.m_pre * 4, c->ws.m_dec * (int64_t)MTP_SPLITK_MAX);
-    const int tiles = gemm_tiles(M, N);
-    int s = 1;
-    while (s < MTP_SPLITK_MAX && tiles * s < 256 && K % (32 * s * 2) == 0 && (int64_t)M * s * 2 <= cap_rows) s *= 2;
-    return s;
+    const int64_t most = std::min<int64_t>(MTP_SPLITK_MAX, cap_rows / std::max(M, 1));
+    return gemm_splits(M, N, K, (int)std::max<int64_t>(most, 1));
 }
 
 // Launch through `f` and, while a step is being recorded, keep it under class `kclass`.

@@ -5,14 +5,15 @@
 // so both operands are K-contiguous.  Outputs go through an epilogue functor
 // that receives 4 consecutive n of one row m.
 //
-//  * gemm_med_bf16: M <= 256 (decode rows of the batched path, the heads).
+//  * gemm_med_bf16: M <= 192 (decode rows of the batched path, the heads),
+//    and products too small for 96 tiles of 64 x 64.
 //    A weight stream (M = 128 rows is ~128 flop per weight byte, below the
 //    MFMA / HBM ridge), so W fragments go straight from HBM into MFMA
 //    registers (no LDS round trip), 16 waves per workgroup split the K range,
 //    each wave loading its own activation fragments from L2 (no LDS staging:
 //    no two waves read the same k), and one LDS reduction over the waves
 //    precedes the epilogue.  The grid is sized so every CU streams.
-//  * gemm_pp_bf16, gemm_duo_bf16: M > 256 (prefill, NAR).  Large tiles on
+//  * gemm_pp_bf16, gemm_duo_bf16: M > 192 (prefill, NAR).  Large tiles on
 //    MFMA with both operands streamed global -> LDS in fragment order.
 // The fp32 model's products are in f32.hip.
 #include <algorithm>
@@ -132,7 +133,26 @@ __global__ __launch_bounds__(64 * GM_NW) void gemm_med_bf16(const bf16_t* __rest
 // Column tiles per workgroup: two, so every activation fragment serves two
 // weight fragments (the activations are re-read once per workgroup), with
 // the LDS reduction holding 16 waves x NT x MT tiles (at most 8).
+//
+// Row tiles MT of a workgroup (med_rows): the fewest (1, 2, 4) that keep the
+// launch within one workgroup per CU.  A workgroup of fewer rows pulls fewer
+// activations through its CU and reduces less in LDS, and its weights are in
+// the XCD's L2 or the memory-side cache from another row group; a second round
+// of workgroups costs more than both save.  Weights cold, MT = 1 / 2 / 4 (us):
+// 32 x 3072 x 1024 4.1 / 4.9 / 5.3, 32 x 4096 x 1024 4.3 / 4.9 / 5.5, 64 x 3072
+// x 1024 - / 4.8 / 6.0, 64 x 4096 x 1024 - / 4.9 / 6.1; past 256 workgroups 32
+// x 6144 x 1536 7.2 / 6.6 / 7.5, 128 x 4096 x 1024 - / 6.9 / 6.1.  A split-K
+// product counts four splits: 32 x 1024 x 1024 2.8 (MT = 1, 4 splits) against
+// 3.0 (MT = 2, 8 splits), 32 x 1536 x 6144 7.6 (MT = 1, 2 splits) against 6.7
+// (MT = 2, 4 splits).
 constexpr int GM_NT = 2;
+static int med_groups(int N) { return ((N + 15) / 16 + GM_NT - 1) / GM_NT; }
+static int med_rows(int M, int N, bool splittable) {
+    const int most = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+    int mt = 1;
+    while (mt < most && med_groups(N) * ((M + 16 * mt - 1) / (16 * mt)) * (splittable ? 4 : 1) > 256) mt *= 2;
+    return mt;
+}
 
 template <int MT, int XP, class Epi>
 static void launch_med(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K, int splits,
@@ -163,7 +183,7 @@ static void launch_med_x(hipStream_t st, const bf16_t* X, int ldx, int M, const 
 }
 
 // ---------------------------------------------------------------- large bf16
-// Prefill, NAR (M > 256) and wide products of fewer rows: tiles of BM rows x
+// Prefill, NAR (M > 192) products: tiles of BM rows x
 // BN columns, 16 x 16 x 32 MFMA.  Both operands are in fragment order
 // (activations written so by their producers, weights packed at load), so a
 // 16 x 32 fragment is one contiguous 1 KB; it travels global -> LDS by one
@@ -176,8 +196,8 @@ static void launch_med_x(hipStream_t st, const bf16_t* X, int ldx, int M, const 
 // that XCD's L2.
 //
 // Two kernels: gemm_pp_bf16 (256 columns, eight waves in two groups that take
-// turns at LDS and the matrix cores) and gemm_duo_bf16 (128 columns, four
-// waves, two workgroups per CU).
+// turns at LDS and the matrix cores) and gemm_duo_bf16 (64 or 128 columns, four
+// waves, two or three workgroups per CU).
 constexpr int GB_NS = 4;
 
 __device__ __forceinline__ constexpr int vmcnt_imm(int n) {
@@ -261,15 +281,16 @@ __device__ __forceinline__ void store_tile(const f32x4_t (&acc)[WFN][WFM], const
     else store_all(std::true_type{});
 }
 
-// The operand fragments of one 32-k step of a wave: 4 of the weights at LDS
+// The operand fragments of one 32-k step of a wave: WFN of the weights at LDS
 // byte address pa, WFM of the activations at pb, 1 KB each.  One asm block
 // issues the reads and waits for them: the compiler cannot tell the stage
 // being read from those the LDS DMA is filling, and would wait for them too.
-template <int WFM>
-__device__ __forceinline__ void pp_read(bf16x8_t (&a)[4], bf16x8_t (&b)[WFM], uint32_t pa, uint32_t pb) {
-    static_assert(WFM >= 4 && WFM <= 8, "row fragments per wave");
+template <int WFN, int WFM>
+__device__ __forceinline__ void pp_read(bf16x8_t (&a)[WFN], bf16x8_t (&b)[WFM], uint32_t pa, uint32_t pb) {
+    static_assert((WFN == 4 && WFM >= 4 && WFM <= 8) || (WFN == 2 && (WFM == 2 || WFM == 4)), "fragments per wave");
+#define PP_A2 "ds_read_b128 %0, %[pa] offset:0\n\tds_read_b128 %1, %[pa] offset:1024\n\t"
 #define PP_A                                                                                       \
-    "ds_read_b128 %0, %[pa] offset:0\n\tds_read_b128 %1, %[pa] offset:1024\n\t"                    \
+    PP_A2                                                                                          \
     "ds_read_b128 %2, %[pa] offset:2048\n\tds_read_b128 %3, %[pa] offset:3072\n\t"                 \
     "ds_read_b128 %4, %[pb] offset:0\n\tds_read_b128 %5, %[pb] offset:1024\n\t"                    \
     "ds_read_b128 %6, %[pb] offset:2048\n\tds_read_b128 %7, %[pb] offset:3072\n\t"
@@ -281,7 +302,14 @@ __device__ __forceinline__ void pp_read(bf16x8_t (&a)[4], bf16x8_t (&b)[WFM], ui
 #define PP_O                                                                                                     \
     "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
 #define PP_I [pa] "v"(pa), [pb] "v"(pb)
-    if constexpr (WFM == 4) asm volatile(PP_A PP_W : PP_O : PP_I : "memory");
+    if constexpr (WFN == 2 && WFM == 2)
+        asm volatile(PP_A2 "ds_read_b128 %2, %[pb] offset:0\n\tds_read_b128 %3, %[pb] offset:1024\n\t" PP_W
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0]), "=&v"(b[1]) : PP_I : "memory");
+    else if constexpr (WFN == 2)
+        asm volatile(PP_A2 "ds_read_b128 %2, %[pb] offset:0\n\tds_read_b128 %3, %[pb] offset:1024\n\t"
+                     "ds_read_b128 %4, %[pb] offset:2048\n\tds_read_b128 %5, %[pb] offset:3072\n\t" PP_W
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3]) : PP_I : "memory");
+    else if constexpr (WFM == 4) asm volatile(PP_A PP_W : PP_O : PP_I : "memory");
     else if constexpr (WFM == 5) asm volatile(PP_A PP_B4 PP_W : PP_O, "=&v"(b[4]) : PP_I : "memory");
     else if constexpr (WFM == 6) asm volatile(PP_A PP_B4 PP_B5 PP_W : PP_O, "=&v"(b[4]), "=&v"(b[5]) : PP_I : "memory");
     else if constexpr (WFM == 7)
@@ -289,6 +317,7 @@ __device__ __forceinline__ void pp_read(bf16x8_t (&a)[4], bf16x8_t (&b)[WFM], ui
     else
         asm volatile(PP_A PP_B4 PP_B5 PP_B6 PP_B7 PP_W
                      : PP_O, "=&v"(b[4]), "=&v"(b[5]), "=&v"(b[6]), "=&v"(b[7]) : PP_I : "memory");
+#undef PP_A2
 #undef PP_A
 #undef PP_B4
 #undef PP_B5
@@ -299,30 +328,54 @@ __device__ __forceinline__ void pp_read(bf16x8_t (&a)[4], bf16x8_t (&b)[WFM], ui
 #undef PP_I
 }
 
-// Tiles of BM = 32 WFM rows x 128 columns, four waves in a 2 x 2 grid, two
-// workgroups per CU (at most 80 KB of stages each): nothing keeps the two in
-// step, so one multiplies while the other reads its operands, starts or stores
-// a tile.  That makes it the kernel for products whose epilogue moves more
-// than their operands (the residual read and written, few tiles per CU): 10678
-// x 1024 x 4096 with the residual 85.9 us (192 rows) against 87.4 with
-// gemm_pp_bf16, 6720 x 1024 x 4096 63.9 (128 rows) against 68.7; and, with 128
-// rows, for products of few tiles.
-template <int WFM, class Epi>
-__global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict__ X, int M, const bf16_t* __restrict__ W,
-                                                    int N, int K, int k_per_split, int tiles_m, int tiles_n, Epi epi) {
-    constexpr int NWV = 4, WFN = 4;
-    constexpr int FM = 2 * WFM, FN = 2 * WFN;   // 16-row fragments of a stage (one 32-k step)
-    constexpr int NF = FM + FN;
-    constexpr int NS = NF <= 20 ? 4 : 3;        // stages: at most 80 KB
+// Waits until at most `left` stages of NL loads each are in flight (left <= MOST).
+template <int MOST, int NL>
+__device__ __forceinline__ void wait_stages(int left) {
+    static_assert(MOST * NL < 64, "vmcnt");
+    if constexpr (MOST == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else if (left >= MOST) __builtin_amdgcn_s_waitcnt(vmcnt_imm(MOST * NL));
+    else wait_stages<MOST - 1, NL>(left);
+}
+
+// Tiles of 32 WFM rows x 32 WFN columns, four waves in a 2 x 2 grid, WGS
+// workgroups per CU (NS stages of KS 32-k steps each, at most 160 / WGS KB):
+// nothing keeps the workgroups of a CU in step, so one multiplies while another
+// reads its operands, starts or stores a tile.  That makes it the kernel for
+// products whose epilogue moves more than their operands (the residual read
+// and written, few tiles per CU; 128 columns): 10678 x 1024 x 4096 with the
+// residual 85.9 us (192 rows) against 87.4 with gemm_pp_bf16, 6720 x 1024 x
+// 4096 63.9 (128 rows) against 68.7; and for products of few tiles.
+//
+// With few tiles what bounds it is a workgroup's serial chain per stage
+// (barrier, operand reads, multiplies: ~700 clocks per 32-k step of a lone
+// 128 x 128 tile, 400 of a 64 x 64 one, whatever the number of stages in
+// flight: 8 stages measured as 4 do), so such products take smaller tiles,
+// three workgroups per CU, and 64 x 64 tiles 64 k per stage, half the
+// barriers.  Weights cold, 128 x 128 / 128 x 64 / 64 x 64 (us): 325 x 3072 x
+// 1024 14.7 / 11.5 / 8.7, 325 x 4096 x 1024 16.2 / 12.4 / 10.5, 1075 x 3072 x
+// 1024 16.2 / 15.0 / 16.7, 1075 x 4096 x 1024 21.2 / 18.4 / 21.2.
+//
+// mfast: tiles are numbered rows first, so an XCD's tiles are neighbours in a
+// column band: each weight is then read by one XCD and the activations by all,
+// the smaller traffic when there are fewer rows than columns (1075 x 4096 x
+// 1024, 128 x 64: 18.4 against 20.7 us).
+template <int WFM, int WFN, int KS, int NS, int WGS, class Epi>
+__global__ __launch_bounds__(256, WGS) void gemm_duo_bf16(const bf16_t* __restrict__ X, int M, const bf16_t* __restrict__ W,
+                                                    int N, int K, int k_per_split, int tiles_m, int tiles_n, int mfast,
+                                                    Epi epi) {
+    constexpr int NWV = 4;
+    constexpr int FM = 2 * WFM, FN = 2 * WFN;   // 16-row fragments of a 32-k step
+    constexpr int NF = (FM + FN) * KS;          // of a stage: row fragments, KS steps each, then columns'
     constexpr int NL = (NF + NWV - 1) / NWV;    // global_load_lds per wave per stage (the last ones may repeat)
+    static_assert(NS * NF * WGS <= 160, "LDS");
     __shared__ __attribute__((aligned(1024))) bf16_t stage[NS * NF * 512];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     // tiles of this workgroup: XCD x (= bid % 8) takes the x-th eighth of the
-    // tiles in row-band order (n fastest), and its workgroups take them in
-    // turn (workgroup j of the XCD: tiles j, j + wgx, ...), so the ones in
-    // flight on an XCD are neighbours in a row band
+    // tiles in row-band order (n fastest; or in column-band order), and its
+    // workgroups take them in turn (workgroup j of the XCD: tiles j, j + wgx,
+    // ...), so the ones in flight on an XCD are neighbours in a band
     const int ntile = tiles_m * tiles_n;
     const int bid = blockIdx.x;
     const int per = (ntile + 7) >> 3;
@@ -333,7 +386,7 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict
     const int mfr_last = ((M + 15) >> 4) - 1, nfr_last = ((N + 15) >> 4) - 1;
     const int split = blockIdx.y;
     const int ks0 = (split * k_per_split) >> 5; // first 32-k step
-    const int nst = k_per_split >> 5;
+    const int nst = k_per_split / (32 * KS);
     const int K32 = K >> 5;
     const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)stage + lane * 16;
     const int r = lane & 15, g = lane >> 4;
@@ -341,17 +394,20 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict
     const bf16_t* src[NL];
     int dst[NL];
     auto set_tile = [&](int tt) {
-        const int tm = tt / tiles_n, tn = tt - tm * tiles_n;
+        const int td = mfast ? tiles_m : tiles_n;
+        const int th = tt / td, tl = tt - th * td;
+        const int tm = mfast ? tl : th, tn = mfast ? th : tl;
         mfr0 = tm * FM;
         nfr0 = tn * FN;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int f = min(wave + NWV * i, NF - 1);
+            const int fk = min(wave + NWV * i, NF - 1);
+            const int f = fk / KS;
             const bf16_t* b;
             if (f < FM) b = X + (size_t)min(mfr0 + f, mfr_last) * K32 * 512;
             else b = W + (size_t)min(nfr0 + f - FM, nfr_last) * K32 * 512;
-            src[i] = b + (size_t)ks0 * 512 + lane * 8;
-            dst[i] = f * 512;
+            src[i] = b + (size_t)(ks0 + fk % KS) * 512 + lane * 8;
+            dst[i] = fk * 512;
         }
     };
     typedef __attribute__((address_space(3))) void lds_void;
@@ -359,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict
         bf16_t* buf = stage + bi * (NF * 512);
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)st * 512), (lds_void*)(buf + dst[i]), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)st * (512 * KS)), (lds_void*)(buf + dst[i]), 16, 0, 0);
     };
     auto issue_first = [&]() {
 #pragma unroll
@@ -383,21 +439,21 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_bf16(const bf16_t* __restrict
             // and every wave is done with the buffer that the next issue
             // refills), refill, consume
             if (later && st == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-            else if (NS == 4 && st + 2 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));
-            else if (st + 1 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
-            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            else wait_stages<NS - 2, NL>(nst - 1 - st);
             gb_barrier();
             const int bn = bi == 0 ? NS - 1 : bi - 1;
             if (st + NS - 1 < nst) issue(st + NS - 1, bn);
             const uint32_t lb = base + bi * (NF * 1024);
-            bf16x8_t a[WFN], b[WFM];
-            pp_read<WFM>(a, b, lb + (FM + wn * WFN) * 1024, lb + wm * WFM * 1024);
+            bf16x8_t a[WFN * KS], b[WFM * KS];
+            pp_read<WFN * KS, WFM * KS>(a, b, lb + (FM + wn * WFN) * (KS * 1024), lb + wm * WFM * (KS * 1024));
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-            for (int i = 0; i < WFN; ++i)
+            for (int u = 0; u < KS; ++u)
 #pragma unroll
-                for (int j = 0; j < WFM; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < WFN; ++i)
+#pragma unroll
+                    for (int j = 0; j < WFM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i * KS + u], b[j * KS + u], acc[i][j], 0, 0, 0);
             __builtin_amdgcn_s_setprio(0);
             bi = bi + 1 == NS ? 0 : bi + 1;
         }
@@ -519,7 +575,7 @@ __global__ __launch_bounds__(512) void gemm_pp_bf16(const bf16_t* __restrict__ X
             const uint32_t lb = base + (st % GB_NS) * (NF * 1024);
             bf16x8_t a[WFN], b[WFM];
             if (st + GB_NS - 1 < nst) issue(st + GB_NS - 1);
-            pp_read<WFM>(a, b, lb + (FM + wn * WFN) * 1024, lb + wm * WFM * 1024);
+            pp_read<WFN, WFM>(a, b, lb + (FM + wn * WFN) * 1024, lb + wm * WFM * 1024);
             if (st + 3 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NL));
             else if (st + 2 < nst) __builtin_amdgcn_s_waitcnt(vmcnt_imm(NL));
             else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -566,15 +622,15 @@ static int cu_count() {
 // most as many workgroups as it holds at once (its CUs times the workgroups
 // per CU that the LDS stages allow), and those take its tiles in turn, so a
 // workgroup's next tile streams in while it stores the last.
-template <int WFM, class Epi>
+template <int WFM, int WFN, int KS, int NS, int WGS, class Epi>
 static hipError_t launch_duo(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, int N, int K, int splits,
-                             Epi epi) {
+                             bool mfast, Epi epi) {
     const int kps = K / splits;
-    if (kps % 32) return hipErrorInvalidValue;
-    const int tm = (M + 32 * WFM - 1) / (32 * WFM), tn = (N + 127) / 128;
-    const int per_xcd = std::min((tm * tn + 7) / 8, cu_count() / 8 * 2);      // two per CU
-    hipLaunchKernelGGL((gemm_duo_bf16<WFM, Epi>), dim3(8 * per_xcd, splits), dim3(256), 0, st, X, M, W, N, K, kps, tm,
-                       tn, epi);
+    if (kps % (32 * KS)) return hipErrorInvalidValue;
+    const int tm = (M + 32 * WFM - 1) / (32 * WFM), tn = (N + 32 * WFN - 1) / (32 * WFN);
+    const int per_xcd = std::min((tm * tn + 7) / 8, cu_count() / 8 * WGS);
+    hipLaunchKernelGGL((gemm_duo_bf16<WFM, WFN, KS, NS, WGS, Epi>), dim3(8 * per_xcd, splits), dim3(256), 0, st, X, M, W, N, K,
+                       kps, tm, tn, mfast ? 1 : 0, epi);
     return hipGetLastError();
 }
 template <int WFM, class Epi>
@@ -590,15 +646,13 @@ static hipError_t launch_pp(hipStream_t st, const bf16_t* X, int M, const bf16_t
 }
 
 // ------------------------------------------------------------------ launchers
-// Tile of an M x N product.  rows: of the eight-wave kernel's
-// tiles (x 256 columns) when wide, of the four-wave kernel's (x 128 columns)
-// otherwise, 0 for the medium kernel (64-row groups, one workgroup per 32 columns).
+// Tile of an M x N product; rows 0: the medium kernel.
 //
-// The eight-wave kernel needs one CU a tile and costs about as much for a
-// tile of 128 rows on a few CUs as on all: with fewer than 192 tiles of 128 x
-// 256 (three quarters of the CUs) the four-wave kernel's 128 x 128 tiles are
-// faster (weights cold: 1075 x 4096 x 1024, 144 against 288 tiles, 26.7
-// against 25.1 us; from 6720 rows and 1024 columns on, 212 tiles, the larger
+// The eight-wave kernel (256 columns) needs one CU a tile and costs about as
+// much for a tile of 128 rows on a few CUs as on all: with fewer than 192
+// tiles of 128 x 256 (three quarters of the CUs) the four-wave kernel's tiles
+// are faster (weights cold: 1075 x 4096 x 1024, 144 against 576 tiles, 22.9
+// against 18.2 us; from 6720 rows and 1024 columns on, 212 tiles, the larger
 // ones win).  The row count is the one with the least rounds x rows: the
 // workgroups take tiles in rounds, and a last round costs as much as a full
 // one (6720 x 3072 x 1024, 27 x 12 tiles of 256 rows, 1.27 rounds: 59.9 us; 42
@@ -606,10 +660,19 @@ static hipError_t launch_pp(hipStream_t st, const bf16_t* X, int M, const bf16_t
 // way: 256 rows 78.9, 192 rows 73.9 us).  32 rows are added for what a round
 // costs whatever its tiles.
 //
-// 128 x 128 when that gives 96 tiles (64 for a split-K product, whose K splits
-// multiply the workgroups).  Measured at M = 325 and 1,075: 72-81 of them
-// without K splits lose to the medium kernel, 96 and more win against it.
-struct BigTile { int rows; bool wide; };
+// Below that, 64 x 64 while all its workgroups are resident at once (three per
+// CU), else 128 x 64 (fewer than 768 tiles here): a second round costs more
+// than the smaller tile saves (1075 x 4096 x 1024, 1088 tiles of 64 x 64, 21.2
+// us, 128 x 64 18.4; 700 x 4096 x 1024, 704 tiles of 64 x 64, 14.5 us, 128 x 64
+// 15.3; 128 x 128, one to two workgroups per CU, 21.2 and 17.5).  A split-K product of a long K with more than 256 tiles of 64
+// x 64 takes 128 x 64 and two splits (1075 x 1024 x 4096: 21.8 us; 64 x 64
+// 22.4 unsplit or split; at K = 1024 8.2 against 9.4 with 64 x 64 unsplit).
+//
+// The medium kernel for up to 192 rows (128 x 3072 x 1024: 6.0 us, 64 x 64
+// 9.0; 200 rows 8.8 against 8.0), and where its workgroups fit one round of
+// the CUs and a split-K product's K is short (325 x 1024 x 1024: 4.7 us
+// unsplit; 64 x 64 in two splits 5.3; at K = 4096 11.7 against 10.4 in four).
+struct BigTile { int rows; int cols; };
 static int tile_count(int M, int N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 // The row count with the least rounds x (rows + 32) over `slots` workgroups.
 static int best_rows(int M, int N, int bn, int slots, int most) {
@@ -623,66 +686,80 @@ static int best_rows(int M, int N, int bn, int slots, int most) {
     }
     return best;
 }
-static BigTile pick_tile(int M, int N, bool splittable, bool resid) {
-    if (tile_count(M, N, 128, 256) >= 192) {
-        // (the residual epilogue's operands leave no registers for 256 rows)
-        if (resid) return {best_rows(M, N, 128, 2 * cu_count(), 224), false};
-        return {best_rows(M, N, 256, cu_count(), 256), true};
-    }
-    if (tile_count(M, N, 128, 128) >= (splittable ? 64 : 96)) return {128, false};
-    return {0, false};
+static bool wide_tiles(int M, int N) { return M > 192 && tile_count(M, N, 128, 256) >= 192; }
+static BigTile pick_tile(int M, int N, int K, bool splittable) {
+    if (M <= 192) return {0, 0};
+    if (wide_tiles(M, N)) return {best_rows(M, N, 256, cu_count(), 256), 256};
+    if (splittable && K < 2048 && med_groups(N) * ((M + 63) / 64) <= 256) return {0, 0};
+    const int t64 = tile_count(M, N, 64, 64), slots = 3 * cu_count();
+    // (64 k per stage; split-K products have K splits of whole stages, see gemm_splits)
+    if (K % 64 == 0 && t64 <= (splittable && K >= 2048 ? cu_count() : slots)) return {64, 64};
+    return {128, 64};
 }
 template <class Epi>
 static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K,
                               int splits, int xpk, Epi epi) {
-    constexpr bool resid = std::is_same<Epi, EpiResid>::value;
+    constexpr bool split = std::is_same<Epi, EpiPartial>::value;
     if (splits < 1 || K % (32 * splits)) return hipErrorInvalidValue;
-    if (M <= 16) {
-        launch_med_x<1>(st, X, ldx, M, W, N, K, splits, xpk, epi);
-    } else if (M <= 32) {
-        launch_med_x<2>(st, X, ldx, M, W, N, K, splits, xpk, epi);
+    if constexpr (std::is_same<Epi, EpiResid>::value) {
+        // (the residual epilogue's operands leave no registers for 256 rows)
+        if (!xpk || !wide_tiles(M, N)) return hipErrorInvalidValue;
+        switch (best_rows(M, N, 128, 2 * cu_count(), 224)) {
+        case 128: return launch_duo<4, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
+        case 160: return launch_duo<5, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
+        case 192: return launch_duo<6, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
+        default: return launch_duo<7, 4, 1, 3, 2>(st, X, M, W, N, K, splits, false, epi);
+        }
     } else {
-        const BigTile bt = pick_tile(M, N, std::is_same<Epi, EpiPartial>::value, resid);
+        const BigTile bt = pick_tile(M, N, K, split);
+        const bool mfast = M <= N;
         if (bt.rows == 0) {
-            launch_med_x<4>(st, X, ldx, M, W, N, K, splits, xpk, epi);
-        } else if (!xpk) {
-            return hipErrorInvalidValue;   // large products take fragment-order activations only
-        } else if constexpr (resid) {
-            switch (bt.rows) {
-            case 128: return launch_duo<4>(st, X, M, W, N, K, splits, epi);
-            case 160: return launch_duo<5>(st, X, M, W, N, K, splits, epi);
-            case 192: return launch_duo<6>(st, X, M, W, N, K, splits, epi);
-            default: return launch_duo<7>(st, X, M, W, N, K, splits, epi);
+            switch (med_rows(M, N, split)) {
+            case 1: launch_med_x<1>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
+            case 2: launch_med_x<2>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
+            default: launch_med_x<4>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
             }
-        } else {
-            if (!bt.wide) return launch_duo<4>(st, X, M, W, N, K, splits, epi);
-            switch (bt.rows) {
-            case 128: return launch_pp<4>(st, X, M, W, N, K, splits, epi);
-            case 160: return launch_pp<5>(st, X, M, W, N, K, splits, epi);
-            case 192: return launch_pp<6>(st, X, M, W, N, K, splits, epi);
-            case 224: return launch_pp<7>(st, X, M, W, N, K, splits, epi);
-            default: return launch_pp<8>(st, X, M, W, N, K, splits, epi);
-            }
+            return hipGetLastError();
+        }
+        if (!xpk) return hipErrorInvalidValue;   // large products take fragment-order activations only
+        if (bt.cols == 64) {
+            if (bt.rows == 64 && K % (64 * splits) == 0)
+                return launch_duo<2, 2, 2, 3, 3>(st, X, M, W, N, K, splits, mfast, epi);
+            return launch_duo<4, 2, 1, 4, 3>(st, X, M, W, N, K, splits, mfast, epi);
+        }
+        switch (bt.rows) {
+        case 128: return launch_pp<4>(st, X, M, W, N, K, splits, epi);
+        case 160: return launch_pp<5>(st, X, M, W, N, K, splits, epi);
+        case 192: return launch_pp<6>(st, X, M, W, N, K, splits, epi);
+        case 224: return launch_pp<7>(st, X, M, W, N, K, splits, epi);
+        default: return launch_pp<8>(st, X, M, W, N, K, splits, epi);
         }
     }
-    return hipGetLastError();
 }
 
-// Whether an M x N bf16 product takes the large-M kernel (the prefill and
+// Whether an M x N bf16 product takes the large-M tiles (the prefill and
 // NAR trunk), where a residual projection updates the residual stream in its
 // epilogue (EPI_RESID) instead of writing split-K partial sums.
-int gemm_resid_in_place(int M, int N) {
-    return M > 256 && pick_tile(M, N, false, true).rows != 0;
-}
+int gemm_resid_in_place(int M, int N) { return M > 256 && wide_tiles(M, N); }
 
-// Workgroups of one split-K-able (partial-sum) bf16 launch for M rows and N
-// columns before K splitting.
-int gemm_tiles(int M, int N) {
-    const int groups = ((N + 15) / 16 + GM_NT - 1) / GM_NT;
-    if (M <= 32) return groups;
-    const BigTile bt = M <= 256 ? BigTile{0, false} : pick_tile(M, N, true, false);
-    if (bt.rows == 0) return groups * ((M + 63) / 64);
-    return tile_count(M, N, bt.rows, bt.wide ? 256 : 128);
+// K splits (a power of two, at most `most`) of a partial-sum product.
+//
+// The medium kernel: up to one workgroup per CU, each split at least 256 k
+// (325 x 1024 x 1024, 192 workgroups: 4.7 us unsplit, 6.5 in two; 32 x 1024 x
+// 1024 2.8 in four, 3.0 in eight; 32 x 1536 x 6144, 48 workgroups: 6.7 in four,
+// 6.9 in eight).  Tiles: up to two workgroups per CU, each split at least 512 k
+// (325 x 1024 x 4096, 96 tiles: 10.4 us in four, 10.8 in eight; 512 x 1024 x
+// 1024, 128 tiles: 5.4 in two, 5.5 in four).  The residual pass that follows
+// reads every split.
+int gemm_splits(int M, int N, int K, int most) {
+    const BigTile bt = pick_tile(M, N, K, true);
+    const int mt = med_rows(M, N, true);
+    const int wgs = bt.rows == 0 ? med_groups(N) * ((M + 16 * mt - 1) / (16 * mt)) : tile_count(M, N, bt.rows, bt.cols);
+    const int limit = bt.rows == 0 ? 256 : 2 * cu_count() + cu_count() / 4, least = bt.rows == 0 ? 256 : 512;
+    const int unit = bt.rows == 64 ? 64 : 32;    // whole stages
+    int s = 1;
+    while (2 * s <= most && wgs * 2 * s <= limit && K % (unit * 2 * s) == 0 && K / (2 * s) >= least) s *= 2;
+    return s;
 }
 
 hipError_t gemm(hipStream_t st, const GemmArgs& a) {

@@ -16,7 +16,7 @@ struct GemmArgs {
     const void* X; int ldx; int M;
     const void* W; int N; int K;
     int splits;           // split-K factor (EPI_PARTIAL only)
-    int xpk;              // bf16 X in MFMA fragment order (frag_off), M <= 256 only
+    int xpk;              // bf16 X in MFMA fragment order (frag_off)
     int opk;              // EPI_GELU: bf16 output in fragment order
     // epilogue operands
     const float* bias;
@@ -31,7 +31,7 @@ struct GemmArgs {
 hipError_t gemm(hipStream_t st, const GemmArgs& a);
 hipError_t gemm_f32(hipStream_t st, const GemmArgs& a);
 bool gemm_f32_ln_ok(int M, int K);
-int gemm_tiles(int M, int N);
+int gemm_splits(int M, int N, int K, int most);
 int gemm_resid_in_place(int M, int N);
 
 struct AttnArgs {

@@ -1,6 +1,7 @@
-"""The large-M products at the edges of their tiles: NAR modules whose row
-counts take each tile height of the eight-wave kernel (128 .. 256 rows), both
-kernels' ragged last tiles, and the first row counts past the medium kernel.
+"""The products at the edges of their tiles: NAR modules whose row counts take
+each row group of the medium kernel, each tile of the four-wave kernel, each
+tile height of the eight-wave kernel (128 .. 256 rows), and their ragged last
+tiles.
 Every row of every utterance is a target, so the stage logits show each output
 row; against the float64 oracle within the bf16 tolerance of test_gpu_nar.py
 (two layers: 3e-2 is twice what twelve show)."""
@@ -13,11 +14,18 @@ from paper_2410_13839_amd.workloads import ModelShape, NarWorkload, make_nar_inp
 
 pytestmark = pytest.mark.gpu
 
-# rows -> the tile heights of the products of 3072 (QKV), 4096 (FFN1) and 1024
-# columns (residual), d 1024 over 256 CUs
+# rows -> the row groups or tiles of the products of 3072 (QKV), 4096 (FFN1) and
+# 1024 columns (split K, or with the residual), d 1024 over 256 CUs
 ROWS = {
-    257: "medium kernel, 128 (four waves), split K",
-    1536: "128 (four waves), 128 (eight waves), 128: the residual in the epilogue from here on",
+    1: "medium kernel, 16-row groups",
+    17: "medium, 16 rows (one in the last group), four splits",
+    33: "medium, 32 rows",
+    65: "medium, 64 rows",
+    192: "medium, 64 rows, the last full group",
+    193: "64 x 64 (one row in the last tile), 64 x 64, medium unsplit / 64 x 64 split",
+    768: "64 x 64 in QKV and FFN1, the most workgroups of three per CU",
+    1025: "128 x 64 (one row in the last tile), 128 x 64, 64 x 64 unsplit / 128 x 64 split",
+    1536: "128 x 64, 128 (eight waves), 64 x 64 / 128 x 64",
     2049: "128, 160 (one row in the last tile), 128",
     2720: "160, 192, 128",
     4001: "192, 256, 128",
