@@ -9,6 +9,23 @@
 // LDS histograms.  A key is prev * V + next; keys are split into buckets of
 // 2^15 consecutive keys (one bucket's histogram fills 128 KB of LDS).
 //
+// A bucket's keys are stored as their 15 low bits.  Valid corpora of at least
+// 2^23 tokens and at most 64 buckets (vocab <= 1448) are read once, in chunks of
+// consecutive positions:
+//
+//   q_ends            per chunk the first utterance that ends in or after it;
+//                     whether the offsets are valid;
+//   q_chunk_sort      one workgroup per chunk: its pairs sorted by bucket in
+//                     LDS and written in one piece, with the bucket's count and
+//                     place in the chunk;
+//   q_chunk_scan      per bucket: exclusive scan of the counts over chunks;
+//   q_bucket_plan     slices of at most S keys per bucket;
+//   q_slice_hist      one workgroup per slice: LDS histogram of its runs,
+//                     written whole to a partial row;
+//   q_reduce          per key: counts += the partials of its bucket's slices.
+//
+// Fewer tokens, more buckets, or offsets that are not ascending within the tokens:
+//
 //   q_bucket_count    utterance ranges per workgroup: validate, count each
 //                     range's pairs per bucket (LDS), row per workgroup;
 //   q_column_scan     per bucket: exclusive scan over workgroups (the
@@ -17,9 +34,9 @@
 //                     overflow check (more pairs than tokens: nothing counted);
 //   q_bucket_scatter  the same pairs again, each key written to its bucket
 //                     at an LDS cursor (every range reads its tokens twice);
-//   q_slice_hist      one workgroup per slice: LDS histogram of its keys,
-//                     written whole to a partial row;
-//   q_reduce          per key: counts += the partials of its bucket's slices.
+//   q_slice_hist, q_reduce  as above.
+// Both sets are launched (whether the offsets are valid is known on the device
+// only); the one that is not needed returns at once.
 // Only a few hundred global atomics remain (input-error tallies).  Every
 // count is an integer sum, so the result does not depend on scheduling.
 #include <hip/hip_runtime.h>
@@ -41,10 +58,18 @@ constexpr int QB_THREADS = 256;                 // count / scatter workgroups
 constexpr int QH_THREADS = 1024;                // histogram workgroups
 constexpr int QS_THREADS = 1024;                // scans
 
+constexpr int QC_THREADS = 512;                 // chunk workgroups
+constexpr int QC_GROUPS = 8;                    // 4-position groups per thread of a chunk
+constexpr int QC_POS = QC_GROUPS * 4 * QC_THREADS;   // positions of a chunk: a bucket's run in it is about 1 KB
+constexpr int QC_NB = 64;                       // buckets of the chunk path
+constexpr int QC_END_WG = 1024;                 // q_ends workgroups
+
 struct QPlan {
     int V, NB, NWG, upw;        // vocab, buckets, range workgroups, utterances per range
     int64_t S;                  // keys per slice
     int64_t max_slices;         // n_tokens / S + NB
+    int nchunk;                 // chunks of the chunk path, 0: general path only
+    int64_t cS;                 // keys per slice of the chunk path (>= S)
 };
 
 struct QWs {
@@ -52,8 +77,13 @@ struct QWs {
     uint32_t* b_cnt;            // [NB]
     uint32_t* b_base;           // [NB + 1]
     uint32_t* s_base;           // [NB + 1] first slice of each bucket
-    uint32_t* ctl;              // [0] 1 when the pairs exceed the key buffer
-    uint32_t* keys;             // [n_tokens]
+    uint32_t* ctl;              // [0] 1 when the pairs exceed the key buffer; chunk path: [1] pairs with
+                                // a bad id, [2] 1 when the offsets are not valid
+    uint16_t* keys;             // [n_tokens] low bits of the keys, by bucket, or by chunk and bucket
+    uint32_t* c_cnt;            // [NB][nchunk] counts, then offsets within the bucket
+    uint32_t* c_lb;             // [NB][nchunk] places of the buckets in a chunk
+    uint32_t* c_bad;            // [nchunk] pairs with a bad id
+    uint32_t* c_first;          // [nchunk] first utterance that ends after the chunk's start
     uint32_t* part;             // [max_slices][QB_BIN]
 };
 
@@ -69,6 +99,10 @@ struct QArgs {
 
 uint64_t align256(uint64_t x) { return (x + 255) & ~uint64_t(255); }
 
+// The key buffer, and the part of it that the chunk path's keys take.
+int64_t key_bytes(int64_t n_tokens) { return (n_tokens > 0 ? (n_tokens + 3) / 4 * 4 : 4) * 4; }
+int64_t chunk_key_bytes(int64_t n_tokens) { return (n_tokens * 2 + 15) / 16 * 16; }
+
 QPlan make_plan(int64_t n_tokens, int64_t n_seqs, int V) {
     QPlan p{};
     p.V = V;
@@ -80,6 +114,18 @@ QPlan make_plan(int64_t n_tokens, int64_t n_seqs, int V) {
     const int64_t s = (n_tokens + 447) / 448;
     p.S = s < 65536 ? 65536 : s;
     p.max_slices = n_tokens / p.S + p.NB;
+    // Chunk path, from 2^23 tokens on (512 chunks, two per CU): below, its
+    // longer chain of launches costs as much as the second sweep (whole estimate,
+    // 4.4 M tokens 82 us against 75, 10.3 M 94 against 100, 20 M 114 against 144).
+    // Its tables take the half of the key buffer that the 16-bit keys leave (the
+    // workspace is sized for 32-bit ones: a call that fits a caller's
+    // workspace keeps fitting it): at most 130 words a chunk of 32 KB.
+    if (p.NB <= QC_NB && n_tokens >= (int64_t(1) << 23) && n_seqs < (int64_t(1) << 31))
+        p.nchunk = (int)((n_tokens + QC_POS - 1) / QC_POS);
+    // one round of histogram workgroups (one per CU): 220 slices' worth of keys
+    // and the rests of 33 buckets
+    const int64_t cs = (n_tokens + 219) / 220;
+    p.cS = cs < p.S ? p.S : cs;
     return p;
 }
 
@@ -93,8 +139,14 @@ uint64_t carve(const QPlan& p, int64_t n_tokens, char* base, QWs* w) {
     t.b_base = (uint32_t*)take((uint64_t)(p.NB + 1) * 4);
     t.s_base = (uint32_t*)take((uint64_t)(p.NB + 1) * 4);
     t.ctl = (uint32_t*)take(16);
-    const int64_t cap = (n_tokens + 3) / 4 * 4;   // whole 16-byte groups for the vector loads
-    t.keys = (uint32_t*)take((uint64_t)(cap > 0 ? cap : 4) * 4);
+    char* kb = take((uint64_t)key_bytes(n_tokens));
+    t.keys = (uint16_t*)kb;
+    if (kb && p.nchunk) {
+        t.c_cnt = (uint32_t*)(kb + chunk_key_bytes(n_tokens));
+        t.c_lb = t.c_cnt + (size_t)p.NB * p.nchunk;
+        t.c_bad = t.c_lb + (size_t)p.NB * p.nchunk;
+        t.c_first = t.c_bad + p.nchunk;
+    }
     t.part = (uint32_t*)take((uint64_t)p.max_slices * QB_BIN * 4);
     if (w) *w = t;
     return o;
@@ -227,9 +279,13 @@ __device__ __forceinline__ uint2 per_utterance(const QArgs& a, const QLds& L, co
     return bad;
 }
 
+// Whether the chunk path has counted (or is counting) this corpus.
+__device__ __forceinline__ bool chunked(const QArgs& a) { return a.p.nchunk != 0 && a.w.ctl[2] == 0; }
+
 __global__ __launch_bounds__(QB_THREADS) void q_bucket_count_kernel(QArgs a) {
     __shared__ uint32_t h[QB_MAX_NB];
     __shared__ QLds L;
+    if (chunked(a)) return;
     const int wg = blockIdx.x, NB = a.p.NB;
     for (int i = threadIdx.x; i < NB; i += QB_THREADS) h[i] = 0;
     __syncthreads();
@@ -288,6 +344,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* s_w, u
 // One workgroup per bucket: prefix over the range workgroups.
 __global__ __launch_bounds__(QS_THREADS) void q_column_scan_kernel(QArgs a) {
     __shared__ uint32_t s_w[QS_THREADS / 64];
+    if (chunked(a)) return;
     const int b = blockIdx.x, NB = a.p.NB, NWG = a.p.NWG;
     uint32_t carry = 0;
     for (int w0 = 0; w0 < NWG; w0 += QS_THREADS) {
@@ -302,15 +359,198 @@ __global__ __launch_bounds__(QS_THREADS) void q_column_scan_kernel(QArgs a) {
     if (threadIdx.x == 0) a.w.b_cnt[b] = carry;
 }
 
+// ------------------------------------------------------------ chunk path
+// Thread per utterance end i (1 .. n_seqs): c_first[c] = i for the chunks that
+// start in [off[i-1], off[i]), so c_first[c] is the first utterance end after
+// the chunk's start; the chunks before the first utterance take 1, those after
+// the last n_seqs + 1.  A workgroup's word of wg_cnt (free until the general path runs)
+// says whether its offsets descend or leave the tokens.
+__global__ __launch_bounds__(256) void q_ends_kernel(QArgs a) {
+    const int64_t pos = QC_POS;
+    bool bad = false;
+    for (int64_t i = 1 + (int64_t)blockIdx.x * 256 + threadIdx.x; i <= a.n_seqs; i += (int64_t)gridDim.x * 256) {
+        const int64_t s = a.off[i - 1], e = a.off[i];
+        if (s < 0 || e < s || e > a.n_tokens) {
+            bad = true;
+            continue;
+        }
+        const int64_t end = i == a.n_seqs ? a.p.nchunk * pos : e;
+        for (int64_t c = i == 1 ? 0 : (s + pos - 1) / pos; c * pos < end; ++c)
+            a.w.c_first[c] = (uint32_t)(c * pos < e ? i : a.n_seqs + 1);
+    }
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) a.w.wg_cnt[blockIdx.x] = any ? 1u : 0u;
+}
+
+// One chunk: its tokens are read once (16-byte groups, the fifth token of a
+// group from the next lane), its pairs' keys kept in registers while each wave
+// ranks them per bucket (LDS counters of its own: the waves of a workgroup do not
+// meet on them), then placed by bucket in LDS and written out in one piece.
+// A chunk's utterance ends are an LDS bitmap, as in the general path.  With
+// offsets that are not valid the result is not used (c_first may then hold
+// anything, so it is bounded here).
+//
+// Bound by memory: 4 bytes a token read, 2 written (105 M tokens 165 us, 3.8
+// TB/s; the two sweeps of the general path with 32-bit keys 114 + 279 us).
+__global__ __launch_bounds__(QC_THREADS) void q_chunk_sort_kernel(QArgs a) {
+    constexpr int GR = QC_GROUPS, POS = QC_POS, NW = QC_THREADS / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t s_sorted[POS];
+    __shared__ uint32_t s_last[POS / 32];
+    __shared__ uint32_t s_cnt[NW * QC_NB];
+    __shared__ uint32_t s_wsum[NW], s_bad[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = blockIdx.x, NB = a.p.NB;
+    const int32_t n = (int32_t)a.n_tokens;
+    const int64_t p0 = (int64_t)c * POS;
+    for (int i = tid; i < POS / 32; i += QC_THREADS) s_last[i] = 0u;
+    s_cnt[tid] = 0u;
+    static_assert(NW * QC_NB == QC_THREADS, "one counter per thread");
+    int4 tv[GR];
+    int t4[GR];
+#pragma unroll
+    for (int q = 0; q < GR; ++q) {
+        const int64_t g = p0 + (int64_t)q * 4 * QC_THREADS + 4 * tid;
+        tv[q] = make_int4(0, 0, 0, 0);
+        if (g + 4 <= n) {
+            tv[q] = *reinterpret_cast<const int4*>(a.tok + g);
+        } else if (g < n) {
+            tv[q].x = a.tok[g];
+            if (g + 1 < n) tv[q].y = a.tok[g + 1];
+            if (g + 2 < n) tv[q].z = a.tok[g + 2];
+        }
+        t4[q] = lane == 63 ? a.tok[g + 4 < n ? g + 4 : n - 1] : 0;
+    }
+    // (bounded by the tokens: the keys written must fit the chunk also when the offsets are not valid)
+    const int64_t S0 = a.off[0], S1 = min(a.off[a.n_seqs], a.n_tokens);
+    __syncthreads();
+    for (int64_t i = (int64_t)max(a.w.c_first[c], 1u) + tid; i <= a.n_seqs; i += QC_THREADS) {
+        const int64_t s = a.off[i - 1], e = a.off[i];
+        const int64_t at = e - 1 - p0;
+        if (e > s && at >= 0 && at < POS) atomicOr(&s_last[at >> 5], 1u << (at & 31));
+        if (e > p0 + POS) break;                 // the later ones end later still
+    }
+    __syncthreads();
+    uint32_t key[GR * 4];
+    uint32_t rank[GR * 2];                       // two 16-bit ranks each
+    uint32_t mask = 0, bad = 0;
+    uint32_t* cnt = s_cnt + wave * QC_NB;
+    const uint32_t V = (uint32_t)a.p.V;
+#pragma unroll
+    for (int q = 0; q < GR; ++q) {
+        int nx = __shfl_down(tv[q].x, 1);
+        if (lane == 63) nx = t4[q];
+        const int t[5] = {tv[q].x, tv[q].y, tv[q].z, tv[q].w, nx};
+        const int l0 = q * 4 * QC_THREADS + 4 * tid;
+        const uint32_t ends = (s_last[l0 >> 5] >> (l0 & 31)) & 15u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t at = p0 + l0 + j;
+            const bool last = (ends >> j) & 1u;
+            const bool pair = at >= S0 && at < S1 && (!last || a.count_eos);
+            const uint32_t x = (uint32_t)t[j], y = last ? (uint32_t)a.eos : (uint32_t)t[j + 1];
+            const bool ok = pair && x < V && y < V;
+            bad += pair && !ok;
+            key[4 * q + j] = ok ? x * V + y : 0u;
+            uint32_t rk = 0;
+            if (ok) {
+                mask |= 1u << (4 * q + j);
+                rk = atomicAdd(&cnt[key[4 * q + j] >> QB_LOG], 1u);
+            }
+            if (j & 1) rank[2 * q + (j >> 1)] |= rk << 16;
+            else rank[2 * q + (j >> 1)] = rk;
+        }
+    }
+    for (int o = 32; o >= 1; o >>= 1) bad += __shfl_xor(bad, o);
+    if (lane == 0) s_bad[wave] = bad;
+    __syncthreads();
+    // places: buckets in order, the waves' shares of one in order
+    const int sl = (tid & (NW - 1)) * QC_NB + tid / NW;      // counter of (bucket tid / NW, wave tid % NW)
+    const uint32_t v = s_cnt[sl];
+    uint32_t x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) s_wsum[wave] = x;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) before += s_wsum[w];
+        total += s_wsum[w];
+    }
+    s_cnt[sl] = before + x - v;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < GR * 4; ++i)
+        if ((mask >> i) & 1u)
+            s_sorted[cnt[key[i] >> QB_LOG] + ((rank[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)] =
+                (uint16_t)(key[i] & (QB_BIN - 1));
+    if (tid < NB) {
+        const uint32_t lb = s_cnt[tid], nx = tid + 1 < QC_NB ? s_cnt[tid + 1] : total;
+        a.w.c_lb[(size_t)tid * a.p.nchunk + c] = lb;
+        a.w.c_cnt[(size_t)tid * a.p.nchunk + c] = nx - lb;
+    }
+    if (tid == 0) {
+        uint32_t b = 0;
+        for (int w = 0; w < NW; ++w) b += s_bad[w];
+        a.w.c_bad[c] = b;
+    }
+    __syncthreads();
+    // (a chunk has at most one pair per position: the last group of eight ends
+    // within the 16-byte-rounded keys)
+    uint4* out = reinterpret_cast<uint4*>(a.w.keys + p0);
+    for (uint32_t i = tid; i < (total + 7) / 8; i += QC_THREADS) out[i] = reinterpret_cast<const uint4*>(s_sorted)[i];
+}
+
+// One workgroup per bucket: exclusive scan of its counts over the chunks,
+// eight consecutive chunks a thread; two more sum the bad pairs and the offset flags.
+__global__ __launch_bounds__(QS_THREADS) void q_chunk_scan_kernel(QArgs a, int n_end_wg) {
+    __shared__ uint32_t s_w[QS_THREADS / 64];
+    const int b = blockIdx.x, NB = a.p.NB, tid = threadIdx.x;
+    constexpr int PER = 8;
+    if (b >= NB) {
+        const uint32_t* src = b == NB ? a.w.c_bad : a.w.wg_cnt;
+        const int m = b == NB ? a.p.nchunk : n_end_wg;
+        uint32_t v = 0, tot;
+        for (int i = tid; i < m; i += QS_THREADS) v += src[i];
+        (void)block_scan_excl(v, s_w, &tot);
+        if (tid == 0) a.w.ctl[b == NB ? 1 : 2] = b == NB ? tot : (tot ? 1u : 0u);
+        return;
+    }
+    uint32_t* col = a.w.c_cnt + (size_t)b * a.p.nchunk;
+    uint32_t carry = 0;
+    for (int c0 = 0; c0 < a.p.nchunk; c0 += QS_THREADS * PER) {
+        uint32_t v[PER], sum = 0, tot;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int c = c0 + PER * tid + j;
+            v[j] = c < a.p.nchunk ? col[c] : 0u;
+            sum += v[j];
+        }
+        uint32_t ex = carry + block_scan_excl(sum, s_w, &tot);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int c = c0 + PER * tid + j;
+            if (c < a.p.nchunk) col[c] = ex;
+            ex += v[j];
+        }
+        carry += tot;
+    }
+    if (tid == 0) a.w.b_cnt[b] = carry;
+}
+
 // One workgroup: bucket bases, slice bases, overflow flag.
 __global__ __launch_bounds__(QS_THREADS) void q_bucket_plan_kernel(QArgs a) {
     __shared__ uint32_t s_w[QS_THREADS / 64];
     const int NB = a.p.NB;
+    const bool ch = chunked(a);
+    const int64_t S = ch ? a.p.cS : a.p.S;
     uint64_t carry = 0, scarry = 0;
     for (int b0 = 0; b0 < NB; b0 += QS_THREADS) {
         const int b = b0 + threadIdx.x;
         const uint32_t c = b < NB ? a.w.b_cnt[b] : 0u;
-        const uint32_t ns = (uint32_t)((c + a.p.S - 1) / a.p.S);
+        const uint32_t ns = (uint32_t)((c + S - 1) / S);
         uint32_t tot, stot;
         const uint32_t ex = block_scan_excl(c, s_w, &tot);
         const uint32_t sex = block_scan_excl(ns, s_w, &stot);
@@ -326,6 +566,8 @@ __global__ __launch_bounds__(QS_THREADS) void q_bucket_plan_kernel(QArgs a) {
         a.w.s_base[NB] = (uint32_t)scarry;
         const bool over = carry > (uint64_t)a.n_tokens || scarry > (uint64_t)a.p.max_slices;
         a.w.ctl[0] = over ? 1u : 0u;
+        if (ch && a.w.ctl[1])
+            __hip_atomic_fetch_add(a.status, (unsigned long long)a.w.ctl[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (over)
             __hip_atomic_fetch_add(a.status + 2, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -344,16 +586,16 @@ __global__ __launch_bounds__(QB_THREADS) void q_bucket_scatter_kernel(QArgs a) {
     __shared__ QLds L;
     __shared__ uint32_t s_sorted[QB_THREADS * 4 * QS_GROUPS];
     __shared__ uint32_t s_cnt[QS_LOCAL_NB], s_lb[QS_LOCAL_NB + 1];
-    if (a.w.ctl[0]) return;
+    if (a.w.ctl[0] || chunked(a)) return;
     const int wg = blockIdx.x, NB = a.p.NB, tid = threadIdx.x;
     const uint32_t* row = a.w.wg_cnt + (size_t)wg * NB;
     for (int i = tid; i < NB; i += QB_THREADS) cur[i] = a.w.b_base[i] + row[i];
     if (tid < QS_LOCAL_NB) s_cnt[tid] = 0;
     __syncthreads();
     const QRange r = range_setup(a, wg, L);
-    uint32_t* keys = a.w.keys;
+    uint16_t* keys = a.w.keys;                       // (a bucket is at most 2^15 keys wide)
     if (!r.flat) {
-        (void)per_utterance(a, L, r, [&](uint32_t key) { keys[atomicAdd(&cur[key >> QB_LOG], 1u)] = key; });
+        (void)per_utterance(a, L, r, [&](uint32_t key) { keys[atomicAdd(&cur[key >> QB_LOG], 1u)] = (uint16_t)(key & (QB_BIN - 1)); });
         return;
     }
     uint32_t dummy = 0;
@@ -363,7 +605,7 @@ __global__ __launch_bounds__(QB_THREADS) void q_bucket_scatter_kernel(QArgs a) {
             const uint32_t m = sweep_group(a, L, r, g0 + 4 * tid, key, &dummy);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if ((m >> j) & 1u) keys[atomicAdd(&cur[key[j] >> QB_LOG], 1u)] = key[j];
+                if ((m >> j) & 1u) keys[atomicAdd(&cur[key[j] >> QB_LOG], 1u)] = (uint16_t)(key[j] & (QB_BIN - 1));
         }
         return;
     }
@@ -397,7 +639,7 @@ __global__ __launch_bounds__(QB_THREADS) void q_bucket_scatter_kernel(QArgs a) {
         const uint32_t total = s_lb[QS_LOCAL_NB];
         for (uint32_t i = tid; i < total; i += QB_THREADS) {
             const uint32_t k = s_sorted[i], b = k >> QB_LOG;
-            keys[cur[b] + (i - s_lb[b])] = k;
+            keys[cur[b] + (i - s_lb[b])] = (uint16_t)(k & (QB_BIN - 1));
         }
         __syncthreads();
         if (tid < NB) {
@@ -420,30 +662,113 @@ __global__ __launch_bounds__(QH_THREADS) void q_slice_hist_kernel(QArgs a) {
         if (a.w.s_base[mid] <= (uint32_t)s) lo = mid; else hi = mid;
     }
     const int b = lo;
-    const uint64_t k0 = a.w.b_base[b] + (uint64_t)(s - a.w.s_base[b]) * a.p.S;
-    uint64_t k1 = k0 + a.p.S;
-    if (k1 > a.w.b_base[b + 1]) k1 = a.w.b_base[b + 1];
+    const bool ch = chunked(a);
+    const int64_t S = ch ? a.p.cS : a.p.S;
     const uint4 z = {0u, 0u, 0u, 0u};
     for (uint32_t i = threadIdx.x; i < QB_BIN / 4; i += QH_THREADS) reinterpret_cast<uint4*>(hist)[i] = z;
     __syncthreads();
-    // aligned 16-byte loads over [k0 & ~3, k1): the key buffer is padded to a
-    // multiple of 4 keys, entries outside [k0, k1) are skipped
-    const uint32_t K0 = (uint32_t)k0, K1 = (uint32_t)k1;
-    constexpr int U = 4;                          // vector loads in flight per thread
-    for (uint32_t blk = (K0 & ~3u) + 4 * threadIdx.x; blk < K1; blk += 4 * QH_THREADS * U) {
-        uint4 v[U];
+    // the keys of one 16-byte group that lie in [k0, k1), k the group's first
+    auto count8 = [&](uint4 v, uint32_t k, uint32_t k0, uint32_t k1) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const uint32_t b4 = blk + 4 * QH_THREADS * j;
-            v[j] = *reinterpret_cast<const uint4*>(a.w.keys + (b4 < K1 ? b4 : blk));
+        for (int j = 0; j < 4; ++j) {
+            if (k + 2 * j >= k0 && k + 2 * j < k1) atomicAdd(&hist[w[j] & 0xFFFFu], 1u);
+            if (k + 2 * j + 1 >= k0 && k + 2 * j + 1 < k1) atomicAdd(&hist[w[j] >> 16], 1u);
         }
+    };
+    if (ch) {
+        // the slice is keys [r0, r1) of the bucket, a run in each of
+        // consecutive chunks; the first of them by a search over the scan
+        const uint32_t r0 = (uint32_t)((uint64_t)(s - a.w.s_base[b]) * S);
+        const uint32_t r1 = (uint32_t)min((uint64_t)r0 + S, (uint64_t)a.w.b_cnt[b]);
+        const uint32_t* pre = a.w.c_cnt + (size_t)b * a.p.nchunk;
+        const uint32_t* lbs = a.w.c_lb + (size_t)b * a.p.nchunk;
+        const int nc = a.p.nchunk, tid = threadIdx.x, lane = tid & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        int base = 0, span = nc;                  // the last chunk c with pre[c] <= r0 is in [base, base + span)
+        while (span > 1) {                        // uniform
+            const int step = (span + QH_THREADS - 1) / QH_THREADS;
+            const int i = tid * step;
+            const int k = __syncthreads_count(i < span && pre[base + i] <= r0);   // k >= 1: pre[base] <= r0
+            span = min(step, span - (k - 1) * step);
+            base += (k - 1) * step;
+        }
+        constexpr int NWV = QH_THREADS / 64;
+        // A wave takes chunks base + wave, + 16, ...: 64 of them at a time, lane j
+        // holding the place of the j-th one's run.  The runs' 16-byte groups are
+        // dealt to the lanes in turn as if they were one sequence (a vector a run
+        // leaves most lanes of every second one idle, and an LDS atomic costs
+        // nearly as much then: 105 M tokens 243 us so, 81 us like this), two vectors on their way while one is
+        // counted.
+        for (int64_t c0 = base + wave; c0 < nc; c0 += 64 * NWV) {
+            const int64_t cj = c0 + (int64_t)NWV * lane;
+            uint32_t st = 0, en = 0;
+            bool in = false;
+            if (cj < nc) {
+                const uint32_t p = pre[cj], q = cj + 1 < nc ? pre[cj + 1] : a.w.b_cnt[b], lb = lbs[cj];
+                const uint32_t f = max(p, r0), t = min(q, r1);
+                in = p < r1;
+                if (f < t) {
+                    st = lb + (f - p);
+                    en = lb + (t - p);
+                }
+            }
+            const int nj = __popcll(__ballot(in));   // the later runs are past the slice
+            const uint32_t ng = en > st ? ((en + 7) >> 3) - (st >> 3) : 0u;
+            uint32_t ge = ng;                         // groups up to and with this run
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(ge, o);
+                if (lane >= o) ge += y;
+            }
+            const uint32_t all = __builtin_amdgcn_readlane(ge, 63);
+            const uint32_t gb = ge - ng;
+            struct Vec { uint32_t k, k0, k1; uint4 v; };
+            int j = 0;                                // the run of this lane's group
+            uint32_t G = lane;
+            auto load = [&](Vec& r) {                 // the lane's next group; all lanes call it
+                while (true) {                        // ends: j stays below 64
+                    const bool up = G >= (uint32_t)__shfl(ge, j) && j < 63;
+                    if (!__any(up)) break;
+                    j += up;
+                }
+                r.k0 = __shfl(st, j);
+                const uint32_t e = __shfl(en, j), g0 = __shfl(gb, j);
+                r.k1 = G < all ? e : 0u;
+                r.k = (r.k0 & ~7u) + 8 * (G - g0);
+                if (r.k < r.k1) r.v = *reinterpret_cast<const uint4*>(a.w.keys + (c0 + (int64_t)NWV * j) * QC_POS + r.k);
+                G += 64;
+            };
+            auto count = [&](const Vec& r) {
+                if (r.k < r.k1) count8(r.v, r.k, r.k0, r.k1);
+            };
+            Vec va{}, vb{};
+            load(va);
+            load(vb);
+            for (uint32_t t = 0; t < all; t += 128) {   // uniform per wave
+                count(va);
+                load(va);
+                count(vb);
+                load(vb);
+            }
+            if (nj < 64) break;                       // uniform per wave
+        }
+    } else {
+        const uint64_t k0 = a.w.b_base[b] + (uint64_t)(s - a.w.s_base[b]) * S;
+        uint64_t k1 = k0 + S;
+        if (k1 > a.w.b_base[b + 1]) k1 = a.w.b_base[b + 1];
+        // aligned 16-byte loads over [k0 & ~7, k1): entries outside [k0, k1)
+        // are skipped
+        const uint32_t K0 = (uint32_t)k0, K1 = (uint32_t)k1;
+        constexpr int U = 4;                      // vector loads in flight per thread
+        for (uint32_t blk = (K0 & ~7u) + 8 * threadIdx.x; blk < K1; blk += 8 * QH_THREADS * U) {
+            uint4 v[U];
 #pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const uint32_t b4 = blk + 4 * QH_THREADS * j;
-            const uint32_t kv[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+            for (int j = 0; j < U; ++j) {
+                const uint32_t b8 = blk + 8 * QH_THREADS * j;
+                v[j] = *reinterpret_cast<const uint4*>(a.w.keys + (b8 < K1 ? b8 : blk));
+            }
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (b4 + c >= K0 && b4 + c < K1) atomicAdd(&hist[kv[c] & (QB_BIN - 1)], 1u);
+            for (int j = 0; j < U; ++j) count8(v[j], blk + 8 * QH_THREADS * j, K0, K1);
         }
     }
     __syncthreads();
@@ -517,6 +842,12 @@ int q_count_run(const int32_t* tokens, int64_t n_tokens, const int64_t* offsets,
     if (n_seqs == 0) return MTP_OK;
     QArgs a{tokens, n_tokens, offsets, n_seqs, eos_id, (flags & MTP_Q_COUNT_EOS) ? 1 : 0, counts,
             reinterpret_cast<unsigned long long*>(status), p, w};
+    if (p.nchunk) {
+        const int ends = (int)(n_seqs < 256 * QC_END_WG ? (n_seqs + 255) / 256 : QC_END_WG);   // <= NWG words of wg_cnt
+        hipLaunchKernelGGL(q_ends_kernel, dim3(ends), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(q_chunk_sort_kernel, dim3(p.nchunk), dim3(QC_THREADS), 0, st, a);
+        hipLaunchKernelGGL(q_chunk_scan_kernel, dim3(p.NB + 2), dim3(QS_THREADS), 0, st, a, ends);
+    }
     hipLaunchKernelGGL(q_bucket_count_kernel, dim3(p.NWG), dim3(QB_THREADS), 0, st, a);
     hipLaunchKernelGGL(q_column_scan_kernel, dim3(p.NB), dim3(QS_THREADS), 0, st, a);
     hipLaunchKernelGGL(q_bucket_plan_kernel, dim3(1), dim3(QS_THREADS), 0, st, a);

@@ -96,6 +96,57 @@ def test_every_counting_path(case):
         _check(toks, offs, V, V - 1, count_eos, 1.0)
 
 
+CHUNK, FROM = 16384, 1 << 23      # positions of a chunk; tokens from which a corpus is counted by chunks
+
+
+def _cut(rng, total, ends):
+    """Ascending offsets over [0, total] that hold `ends` and random ones, a few utterances empty."""
+    cuts = np.concatenate([ends, rng.integers(0, total + 1, size=total // 200 + 1)])
+    cuts = np.concatenate([cuts, cuts[:3]])
+    return np.sort(cuts[(cuts >= 0) & (cuts <= total)]).astype(np.int64)
+
+
+@pytest.mark.parametrize("total,ends", [
+    (1, [0, 1]), (139, [0, 139]), (4097, [3, 4096]),
+    (FROM - 1, [0, 3 * CHUNK, FROM - 1]),                     # the last of the general path
+    (FROM, [0, CHUNK, FROM]),                                 # an end on a boundary
+    (FROM + 1, [7, 2 * CHUNK + 1, FROM]),                     # tokens before the first utterance and past the last
+    (FROM + CHUNK - 3, [CHUNK - 1, CHUNK + 1, FROM + CHUNK - 3])])
+def test_chunk_edges(total, ends):
+    rng = np.random.default_rng(total)
+    toks = rng.integers(0, VOCAB - 1, size=total).astype(np.int32)
+    if total > 100:
+        toks[rng.integers(0, total, size=5)] = VOCAB                  # bad ids are tallied once
+    ends = np.array(ends, np.int64)
+    for offs in (_cut(rng, total, ends), ends):                       # many utterances; one or two long ones
+        if ends[0] > 0:
+            offs = offs[offs >= ends[0]]
+        for count_eos in (False, True):
+            _check(toks, offs, VOCAB, EOS_ID, count_eos, 0.5)
+
+
+@pytest.mark.parametrize("V", [1, 2, 181, 182, 1448, 1449])           # 1, 1, 1, 2, 64 and 65 buckets
+def test_bucket_edges(V):
+    rng = np.random.default_rng(V)
+    toks = rng.integers(0, V, size=FROM + 11).astype(np.int32)
+    toks[FROM - 30000:] = V - 1                                            # one bucket gets most of a chunk
+    offs = _cut(rng, toks.size, np.array([0, 9000, toks.size]))
+    _check(toks, offs, V, V - 1, True, 1.0)
+
+
+def test_descending_offsets_over_many_chunks():
+    """The chunk path's result is dropped and its tallies are not added."""
+    rng = np.random.default_rng(8)
+    toks = rng.integers(0, VOCAB - 1, size=FROM + 100).astype(np.int32)
+    toks[[5, 12345, FROM]] = -1
+    offs = _cut(rng, toks.size, np.array([0, toks.size]))
+    # 40 pairs twice, fewer than the 40,000 utterances without an EOS pair leave out (more pairs
+    # than tokens would be refused)
+    offs[len(offs) // 2] = offs[len(offs) // 2 - 1] - 40
+    offs[-1] += 4
+    _check(toks, offs, VOCAB, EOS_ID, False, 0.5)
+
+
 def test_empty_corpora():
     for toks, offs in ((np.zeros(0, np.int32), np.zeros(1, np.int64)),
                        (np.zeros(0, np.int32), np.zeros(4, np.int64)),
