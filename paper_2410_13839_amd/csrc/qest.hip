@@ -279,13 +279,17 @@ __device__ __forceinline__ uint2 per_utterance(const QArgs& a, const QLds& L, co
     return bad;
 }
 
-// Whether the chunk path has counted (or is counting) this corpus.
-__device__ __forceinline__ bool chunked(const QArgs& a) { return a.p.nchunk != 0 && a.w.ctl[2] == 0; }
+// Whether the chunk path has counted (or is counting) this corpus.  CHUNKS, a
+// template argument of the kernels of both paths: that path was launched; the
+// small corpora's kernels neither ask nor hold its code.
+template <bool CHUNKS>
+__device__ __forceinline__ bool chunked(const QArgs& a) { return CHUNKS && a.w.ctl[2] == 0; }
 
+template <bool CHUNKS>
 __global__ __launch_bounds__(QB_THREADS) void q_bucket_count_kernel(QArgs a) {
     __shared__ uint32_t h[QB_MAX_NB];
     __shared__ QLds L;
-    if (chunked(a)) return;
+    if (chunked<CHUNKS>(a)) return;
     const int wg = blockIdx.x, NB = a.p.NB;
     for (int i = threadIdx.x; i < NB; i += QB_THREADS) h[i] = 0;
     __syncthreads();
@@ -342,9 +346,10 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* s_w, u
 }
 
 // One workgroup per bucket: prefix over the range workgroups.
+template <bool CHUNKS>
 __global__ __launch_bounds__(QS_THREADS) void q_column_scan_kernel(QArgs a) {
     __shared__ uint32_t s_w[QS_THREADS / 64];
-    if (chunked(a)) return;
+    if (chunked<CHUNKS>(a)) return;
     const int b = blockIdx.x, NB = a.p.NB, NWG = a.p.NWG;
     uint32_t carry = 0;
     for (int w0 = 0; w0 < NWG; w0 += QS_THREADS) {
@@ -541,10 +546,11 @@ __global__ __launch_bounds__(QS_THREADS) void q_chunk_scan_kernel(QArgs a, int n
 }
 
 // One workgroup: bucket bases, slice bases, overflow flag.
+template <bool CHUNKS>
 __global__ __launch_bounds__(QS_THREADS) void q_bucket_plan_kernel(QArgs a) {
     __shared__ uint32_t s_w[QS_THREADS / 64];
     const int NB = a.p.NB;
-    const bool ch = chunked(a);
+    const bool ch = chunked<CHUNKS>(a);
     const int64_t S = ch ? a.p.cS : a.p.S;
     uint64_t carry = 0, scarry = 0;
     for (int b0 = 0; b0 < NB; b0 += QS_THREADS) {
@@ -581,12 +587,13 @@ __global__ __launch_bounds__(QS_THREADS) void q_bucket_plan_kernel(QArgs a) {
 constexpr int QS_LOCAL_NB = 64;
 constexpr int QS_GROUPS = 2;                        // 4-position groups per thread per round
 
+template <bool CHUNKS>
 __global__ __launch_bounds__(QB_THREADS) void q_bucket_scatter_kernel(QArgs a) {
     __shared__ uint32_t cur[QB_MAX_NB];
     __shared__ QLds L;
     __shared__ uint32_t s_sorted[QB_THREADS * 4 * QS_GROUPS];
     __shared__ uint32_t s_cnt[QS_LOCAL_NB], s_lb[QS_LOCAL_NB + 1];
-    if (a.w.ctl[0] || chunked(a)) return;
+    if (a.w.ctl[0] || chunked<CHUNKS>(a)) return;
     const int wg = blockIdx.x, NB = a.p.NB, tid = threadIdx.x;
     const uint32_t* row = a.w.wg_cnt + (size_t)wg * NB;
     for (int i = tid; i < NB; i += QB_THREADS) cur[i] = a.w.b_base[i] + row[i];
@@ -650,6 +657,7 @@ __global__ __launch_bounds__(QB_THREADS) void q_bucket_scatter_kernel(QArgs a) {
     }
 }
 
+template <bool CHUNKS>
 __global__ __launch_bounds__(QH_THREADS) void q_slice_hist_kernel(QArgs a) {
     extern __shared__ uint32_t hist[];            // QB_BIN entries
     if (a.w.ctl[0]) return;
@@ -662,7 +670,7 @@ __global__ __launch_bounds__(QH_THREADS) void q_slice_hist_kernel(QArgs a) {
         if (a.w.s_base[mid] <= (uint32_t)s) lo = mid; else hi = mid;
     }
     const int b = lo;
-    const bool ch = chunked(a);
+    const bool ch = chunked<CHUNKS>(a);
     const int64_t S = ch ? a.p.cS : a.p.S;
     const uint4 z = {0u, 0u, 0u, 0u};
     for (uint32_t i = threadIdx.x; i < QB_BIN / 4; i += QH_THREADS) reinterpret_cast<uint4*>(hist)[i] = z;
@@ -829,7 +837,29 @@ int q_count_check(const int32_t* tokens, int64_t n_tokens, const int64_t* offset
     return MTP_OK;
 }
 
-// Validation and the six launches of a count over a workspace of ws_bytes.
+// The count's launches up to the partial rows.
+template <bool CHUNKS>
+int q_launch(const QArgs& a, hipStream_t st) {
+    const QPlan& p = a.p;
+    if constexpr (CHUNKS) {
+        const int ends = (int)(a.n_seqs < 256 * QC_END_WG ? (a.n_seqs + 255) / 256 : QC_END_WG);   // <= NWG words of wg_cnt
+        hipLaunchKernelGGL(q_ends_kernel, dim3(ends), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(q_chunk_sort_kernel, dim3(p.nchunk), dim3(QC_THREADS), 0, st, a);
+        hipLaunchKernelGGL(q_chunk_scan_kernel, dim3(p.NB + 2), dim3(QS_THREADS), 0, st, a, ends);
+    }
+    hipLaunchKernelGGL(q_bucket_count_kernel<CHUNKS>, dim3(p.NWG), dim3(QB_THREADS), 0, st, a);
+    hipLaunchKernelGGL(q_column_scan_kernel<CHUNKS>, dim3(p.NB), dim3(QS_THREADS), 0, st, a);
+    hipLaunchKernelGGL(q_bucket_plan_kernel<CHUNKS>, dim3(1), dim3(QS_THREADS), 0, st, a);
+    hipLaunchKernelGGL(q_bucket_scatter_kernel<CHUNKS>, dim3(p.NWG), dim3(QB_THREADS), 0, st, a);
+    // 128 KB of dynamic LDS: raise the function's limit (per device, cheap)
+    if (hipFuncSetAttribute((const void*)q_slice_hist_kernel<CHUNKS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            QB_BIN * 4) != hipSuccess)
+        return MTP_EHIP;
+    hipLaunchKernelGGL(q_slice_hist_kernel<CHUNKS>, dim3((unsigned)p.max_slices), dim3(QH_THREADS), QB_BIN * 4, st, a);
+    return MTP_OK;
+}
+
+// Validation and the launches of a count over a workspace of ws_bytes.
 int q_count_run(const int32_t* tokens, int64_t n_tokens, const int64_t* offsets, int64_t n_seqs, int vocab,
                 int eos_id, int flags, uint32_t* counts, uint64_t* status, void* workspace, uint64_t ws_bytes,
                 hipStream_t st) {
@@ -842,21 +872,8 @@ int q_count_run(const int32_t* tokens, int64_t n_tokens, const int64_t* offsets,
     if (n_seqs == 0) return MTP_OK;
     QArgs a{tokens, n_tokens, offsets, n_seqs, eos_id, (flags & MTP_Q_COUNT_EOS) ? 1 : 0, counts,
             reinterpret_cast<unsigned long long*>(status), p, w};
-    if (p.nchunk) {
-        const int ends = (int)(n_seqs < 256 * QC_END_WG ? (n_seqs + 255) / 256 : QC_END_WG);   // <= NWG words of wg_cnt
-        hipLaunchKernelGGL(q_ends_kernel, dim3(ends), dim3(256), 0, st, a);
-        hipLaunchKernelGGL(q_chunk_sort_kernel, dim3(p.nchunk), dim3(QC_THREADS), 0, st, a);
-        hipLaunchKernelGGL(q_chunk_scan_kernel, dim3(p.NB + 2), dim3(QS_THREADS), 0, st, a, ends);
-    }
-    hipLaunchKernelGGL(q_bucket_count_kernel, dim3(p.NWG), dim3(QB_THREADS), 0, st, a);
-    hipLaunchKernelGGL(q_column_scan_kernel, dim3(p.NB), dim3(QS_THREADS), 0, st, a);
-    hipLaunchKernelGGL(q_bucket_plan_kernel, dim3(1), dim3(QS_THREADS), 0, st, a);
-    hipLaunchKernelGGL(q_bucket_scatter_kernel, dim3(p.NWG), dim3(QB_THREADS), 0, st, a);
-    // 128 KB of dynamic LDS: raise the function's limit (per device, cheap)
-    if (hipFuncSetAttribute((const void*)q_slice_hist_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            QB_BIN * 4) != hipSuccess)
-        return MTP_EHIP;
-    hipLaunchKernelGGL(q_slice_hist_kernel, dim3((unsigned)p.max_slices), dim3(QH_THREADS), QB_BIN * 4, st, a);
+    const int rc2 = p.nchunk ? q_launch<true>(a, st) : q_launch<false>(a, st);
+    if (rc2 != MTP_OK) return rc2;
     const uint64_t nk = (uint64_t)vocab * vocab;
     hipLaunchKernelGGL(q_reduce_kernel, dim3((unsigned)((nk + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? MTP_OK : MTP_EHIP;
