@@ -703,8 +703,8 @@ static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, c
     if (splits < 1 || K % (32 * splits)) return hipErrorInvalidValue;
     if constexpr (std::is_same<Epi, EpiResid>::value) {
         // (the residual epilogue's operands leave no registers for 256 rows)
-        if (!xpk || !wide_tiles(M, N)) return hipErrorInvalidValue;
-        switch (best_rows(M, N, 128, 2 * cu_count(), 224)) {
+        if (!xpk || !gemm_resid_in_place(M, N)) return hipErrorInvalidValue;
+        switch (wide_tiles(M, N) ? best_rows(M, N, 128, 2 * cu_count(), 224) : 128) {
         case 128: return launch_duo<4, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
         case 160: return launch_duo<5, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
         case 192: return launch_duo<6, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
@@ -740,7 +740,13 @@ static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, c
 // Whether an M x N bf16 product takes the large-M tiles (the prefill and
 // NAR trunk), where a residual projection updates the residual stream in its
 // epilogue (EPI_RESID) instead of writing split-K partial sums.
-int gemm_resid_in_place(int M, int N) { return M > 256 && wide_tiles(M, N); }
+// From wide tiles on, and where 64 x 64 tiles no longer fit one round (then with
+// 128 x 128): 84 layers of 4300 rows, d 1024, 20.1 ms against 21.5 with partial sums, 5375
+// rows 23.0 against 24.6, 3225 rows 16.6 either way; below, partial sums (2600
+// rows: 78 us of products and residual passes a layer against 84).
+int gemm_resid_in_place(int M, int N) {
+    return M > 256 && (wide_tiles(M, N) || tile_count(M, N, 64, 64) > 3 * cu_count());
+}
 
 // K splits (a power of two, at most `most`) of a partial-sum product.
 //

@@ -26,9 +26,9 @@ ROWS = {
     768: "64 x 64 in QKV and FFN1, the most workgroups of three per CU",
     1025: "128 x 64 (one row in the last tile), 128 x 64, 64 x 64 unsplit / 128 x 64 split",
     1536: "128 x 64, 128 (eight waves), 64 x 64 / 128 x 64",
-    2049: "128, 160 (one row in the last tile), 128",
-    2720: "160, 192, 128",
-    4001: "192, 256, 128",
+    2049: "128, 160 (one row in the last tile), 64 x 64 / 128 x 64",
+    2720: "160, 192, 64 x 64 / 128 x 64",
+    4001: "192, 256, 128 with the residual",
     4090: "224, 256, 128",
     8209: "224, 192, 160",
     10250: "256, 224, 192",
