@@ -876,9 +876,12 @@ static hipError_t gemv_part_merge(hipStream_t st, const GemvArgs& a) {
 
 // Largest attention split count the out-projection can merge for M rows of
 // width d: each thread keeps at most 8 splits of one (row, float4) item, and
-// the workgroup's 1024 threads cover the items GS times over; 0 if none.
+// the workgroup's 1024 threads cover the items GS times over; 0 if none, or
+// if its K range (a quarter of d) holds more items than threads (from 11 rows
+// on at d 1536, from 9 at d 2048), where the merge is a launch of its own.
 int gemv_merge_max_splits(int M, int d) {
     if (M < 1 || M > 16 || d > 2048) return 0;
+    if (M * (d / 16) > 64 * GV_NW) return 0;
     int mr = 1;
     while (mr < M) mr <<= 1;
     const int kch = d > 1024 ? 2 : 1;

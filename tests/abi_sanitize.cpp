@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../include/mtp.h"
+#include "../paper_2410_13839_amd/csrc/launch.h"
 
 static int failures = 0;
 #define CHECK(cond)                                                        \
@@ -202,6 +203,16 @@ int main() {
         CHECK(mtp_q_normalize(counts, 1025, -1.f, static_cast<float*>(fake(11)), nullptr) == MTP_EINVAL);
         CHECK(mtp_q_normalize(counts, 0, 1.f, static_cast<float*>(fake(11)), nullptr) == MTP_EINVAL);
     }
+    // ---- the key splits that the small-batch out-projection merges: every
+    //      (row, 4 columns) item of its K range (a quarter of d) has a thread
+    //      of its 1024, eight splits a thread at most
+    for (int d = 256; d <= 2048; d += 256)
+        for (int M = 1; M <= 16; ++M) {
+            const int n = mtp::gemv_merge_max_splits(M, d), items = M * (d / 16);
+            CHECK(n >= 0 && n <= 32 && (n == 0 || items <= 1024));
+            CHECK(n <= 8 * std::max(1, 1024 / items));
+            if (d <= 1024) CHECK(n >= 8);
+        }
     if (failures) {
         std::fprintf(stderr, "%d checks failed\n", failures);
         return 1;
