@@ -160,10 +160,12 @@ __global__ __launch_bounds__(512) void select_fused_kernel(SelectArgs a) {
         const bool mask_eos = (st0.gen + t) < a.eos_min;
         // unconditional loads from clamped indices (a predicated load would
         // become a branch and a full wait per element); entries past the
-        // vocabulary are excluded by the idx < V test of the selection
+        // vocabulary are excluded by the idx < V test of the selection.  A
+        // NaN counts as -infinity: it would lose every comparison, and a head
+        // with fewer than k numbers would end with an id outside the vocabulary
         float v[PER_LANE];
 #pragma unroll
-        for (int j = 0; j < PER_LANE; ++j) v[j] = lg[min(lane + 64 * j, V - 1)];
+        for (int j = 0; j < PER_LANE; ++j) v[j] = fmaxf(lg[min(lane + 64 * j, V - 1)], -INFINITY);
 #pragma unroll
         for (int j = 0; j < PER_LANE; ++j)
             if (lane + 64 * j == a.eos_id && mask_eos) v[j] = -INFINITY;
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(512) void select_fused_kernel(SelectArgs a) {
         for (int idx = tid; idx < K * m; idx += blockDim.x) {
             const int tt = udiv_small(idx, m), j = idx - tt * m;
             const int c = s_U[j];
-            float l = lgb[(size_t)tt * V + c];
+            float l = fmaxf(lgb[(size_t)tt * V + c], -INFINITY);
             if (c == a.eos_id && (st0.gen + tt) < a.eos_min) l = -INFINITY;
             s_ue[tt][j] = l - s_top[tt];
         }
@@ -338,7 +340,8 @@ __global__ __launch_bounds__(512) void select_fused_kernel(SelectArgs a) {
                 if (uni) out_ue[tt * UMAX + j] = et;
             }
         }
-        float bestd = (j < m) ? delta : -INFINITY;
+        // (a score may be NaN, inf - inf; the last state is one of the m all the same)
+        float bestd = (j < m) ? fmaxf(delta, -INFINITY) : -INFINITY;
         int last = (j < m) ? j : UMAX + j;
         wave_argmax_uniform(bestd, last);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
