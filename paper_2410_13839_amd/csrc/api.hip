@@ -294,6 +294,25 @@ int hip_fail(mtp_ctx* c, hipError_t e, const char* where) {
         if (_e != hipSuccess) return hip_fail((ctx), _e, (where)); \
     } while (0)
 
+// Copies to host memory (a NULL destination: none), then the wait for them.
+// The wait also follows a copy that failed: an earlier one must not still be
+// writing memory of the caller when the call returns.
+struct ToHost {
+    mtp_ctx* c;
+    hipError_t e = hipSuccess;
+    const char* at = "";
+    void add(void* dst, const void* src, size_t bytes, const char* where) {
+        if (!dst || e != hipSuccess) return;
+        e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream);
+        at = where;
+    }
+    int wait(const char* where = "sync") {
+        const hipError_t s = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, at);
+        return s != hipSuccess ? hip_fail(c, s, where) : MTP_OK;
+    }
+};
+
 int pick_splits(const mtp_ctx* c, int M, int N, int K) {
     if (c->cfg.dtype != MTP_DTYPE_BF16) return 1;
     const int64_t cap_rows = std::max(c->ws.m_pre * 4, c->ws.m_dec * (int64_t)MTP_SPLITK_MAX);
@@ -1042,19 +1061,19 @@ int mtp_decode_step(mtp_ctx* c, int K, int top_k, int32_t* out_tokens, int32_t* 
     if (!out_tokens || !out_count) { if (c) c->err = "NULL output"; return MTP_EINVAL; }
     int rc = step_common(c, K, top_k);
     if (rc) return rc;
-    HIPCHK(c, hipMemcpyAsync(out_tokens, c->WS() + c->ws.out_tok, (size_t)c->B * K * 4, hipMemcpyDeviceToHost, c->stream), "tokens to host");
-    HIPCHK(c, hipMemcpyAsync(out_count, c->WS() + c->ws.out_cnt, (size_t)c->B * 4, hipMemcpyDeviceToHost, c->stream), "counts to host");
     unsigned waits_out[2] = {0, 0};
+    ToHost out{c};
+    out.add(out_tokens, c->WS() + c->ws.out_tok, (size_t)c->B * K * 4, "tokens to host");
+    out.add(out_count, c->WS() + c->ws.out_cnt, (size_t)c->B * 4, "counts to host");
     // (each word exists, zeroed, once its launch has been planned)
     unsigned* werr = c->xcd_deal == 1 ? c->ws_ptr<unsigned>(c->ws.fsync) + 3 * (3 * c->cfg.d_model / 16) : nullptr;
     unsigned* ferr = c->ffn_ready == 1
                          ? reinterpret_cast<unsigned*>(c->ws_ptr<bf16_t>(c->ws.ffs) + (size_t)3 * 16 * c->cfg.d_ff)
                          : nullptr;
-    if (werr)
-        HIPCHK(c, hipMemcpyAsync(&waits_out[0], werr, 4, hipMemcpyDeviceToHost, c->stream), "front wait count");
-    if (ferr)
-        HIPCHK(c, hipMemcpyAsync(&waits_out[1], ferr, 4, hipMemcpyDeviceToHost, c->stream), "ffn wait count");
-    HIPCHK(c, hipStreamSynchronize(c->stream), "step sync");
+    if (werr) out.add(&waits_out[0], werr, 4, "front wait count");
+    if (ferr) out.add(&waits_out[1], ferr, 4, "ffn wait count");
+    rc = out.wait("step sync");
+    if (rc) return rc;
     if (waits_out[0] || waits_out[1]) {
         // a one-launch front or FFN went on with data it could not see
         // complete: the tokens and the sequences' state are not those of
@@ -1091,14 +1110,13 @@ int mtp_get_lattice(mtp_ctx* c, int32_t* cand, float* ehat, float* delta, int32_
     if (!c) return MTP_EINVAL;
     if (!c->last_K) { c->err = "no decode step yet"; return MTP_ESTATE; }
     const size_t n = (size_t)c->B * c->last_K * c->last_topk * 4;
-    hipStream_t st = c->stream;
-    if (cand) HIPCHK(c, hipMemcpyAsync(cand, c->WS() + c->ws.cand, n, hipMemcpyDeviceToHost, st), "cand");
-    if (ehat) HIPCHK(c, hipMemcpyAsync(ehat, c->WS() + c->ws.ehat, n, hipMemcpyDeviceToHost, st), "ehat");
-    if (delta) HIPCHK(c, hipMemcpyAsync(delta, c->WS() + c->ws.delta, n, hipMemcpyDeviceToHost, st), "delta");
-    if (psi) HIPCHK(c, hipMemcpyAsync(psi, c->WS() + c->ws.psi, n, hipMemcpyDeviceToHost, st), "psi");
-    if (slots) HIPCHK(c, hipMemcpyAsync(slots, c->WS() + c->ws.slots, (size_t)c->B * c->last_K * 4, hipMemcpyDeviceToHost, st), "slots");
-    HIPCHK(c, hipStreamSynchronize(st), "sync");
-    return MTP_OK;
+    ToHost out{c};
+    out.add(cand, c->WS() + c->ws.cand, n, "cand");
+    out.add(ehat, c->WS() + c->ws.ehat, n, "ehat");
+    out.add(delta, c->WS() + c->ws.delta, n, "delta");
+    out.add(psi, c->WS() + c->ws.psi, n, "psi");
+    out.add(slots, c->WS() + c->ws.slots, (size_t)c->B * c->last_K * 4, "slots");
+    return out.wait();
 }
 
 int mtp_force_tokens(mtp_ctx* c, const int32_t* tokens, const int32_t* count) {
@@ -1111,9 +1129,10 @@ int mtp_force_tokens(mtp_ctx* c, const int32_t* tokens, const int32_t* count) {
     hipStream_t st = c->stream;
     std::vector<SeqState> s(B);
     std::vector<int32_t> n_old(B);
-    HIPCHK(c, hipMemcpyAsync(s.data(), c->WS() + c->ws.state, B * sizeof(SeqState), hipMemcpyDeviceToHost, st), "state to host");
-    HIPCHK(c, hipMemcpyAsync(n_old.data(), c->WS() + c->ws.out_cnt, B * 4, hipMemcpyDeviceToHost, st), "counts to host");
-    HIPCHK(c, hipStreamSynchronize(st), "sync");
+    ToHost old{c};
+    old.add(s.data(), c->WS() + c->ws.state, B * sizeof(SeqState), "state to host");
+    old.add(n_old.data(), c->WS() + c->ws.out_cnt, B * 4, "counts to host");
+    if (const int rc = old.wait()) return rc;
     // validate everything before changing anything
     for (int b = 0; b < B; ++b) {
         const int n = count[b], g0 = s[b].gen - n_old[b];
@@ -1172,15 +1191,14 @@ int mtp_get_union_lattice(mtp_ctx* c, int32_t* m, int32_t* states, float* ehat, 
     if (!c->last_K) { c->err = "no decode step yet"; return MTP_ESTATE; }
     if (c->last_lattice != MTP_LATTICE_UNION) { c->err = "the last step did not use the union lattice"; return MTP_ESTATE; }
     const size_t B = c->B, n = B * MTP_MAX_HEADS_K * 64 * 4;
-    hipStream_t st = c->stream;
-    if (m) HIPCHK(c, hipMemcpyAsync(m, c->WS() + c->ws.u_m, B * 4, hipMemcpyDeviceToHost, st), "m");
-    if (states) HIPCHK(c, hipMemcpyAsync(states, c->WS() + c->ws.u_states, B * 64 * 4, hipMemcpyDeviceToHost, st), "states");
-    if (ehat) HIPCHK(c, hipMemcpyAsync(ehat, c->WS() + c->ws.u_ehat, n, hipMemcpyDeviceToHost, st), "ehat");
-    if (delta) HIPCHK(c, hipMemcpyAsync(delta, c->WS() + c->ws.u_delta, n, hipMemcpyDeviceToHost, st), "delta");
-    if (psi) HIPCHK(c, hipMemcpyAsync(psi, c->WS() + c->ws.u_psi, n, hipMemcpyDeviceToHost, st), "psi");
-    if (slots) HIPCHK(c, hipMemcpyAsync(slots, c->WS() + c->ws.slots, B * c->last_K * 4, hipMemcpyDeviceToHost, st), "slots");
-    HIPCHK(c, hipStreamSynchronize(st), "sync");
-    return MTP_OK;
+    ToHost out{c};
+    out.add(m, c->WS() + c->ws.u_m, B * 4, "m");
+    out.add(states, c->WS() + c->ws.u_states, B * 64 * 4, "states");
+    out.add(ehat, c->WS() + c->ws.u_ehat, n, "ehat");
+    out.add(delta, c->WS() + c->ws.u_delta, n, "delta");
+    out.add(psi, c->WS() + c->ws.u_psi, n, "psi");
+    out.add(slots, c->WS() + c->ws.slots, B * c->last_K * 4, "slots");
+    return out.wait();
 }
 
 int mtp_set_sampling(mtp_ctx* c, int mode, float temperature, uint64_t seed) {
@@ -1376,15 +1394,14 @@ int mtp_nar_get_logits(mtp_ctx* c, int stage, float* logits) {
     size_t runs = 0;
     for (size_t i = 0; i < tgt.size(); ++i) runs += i == 0 || tgt[i] != tgt[i - 1] + 1;
     if (tgt.size() * (size_t)cb * 4 >= runs * 65536) {
+        ToHost out{c};
         for (size_t i = 0; i < tgt.size();) {
             size_t e = i + 1;
             while (e < tgt.size() && tgt[e] == tgt[e - 1] + 1) ++e;
-            HIPCHK(c, hipMemcpyAsync(logits + i * cb, src + (size_t)tgt[i] * cb * 4, (e - i) * cb * 4,
-                                     hipMemcpyDeviceToHost, c->stream), "logits to host");
+            out.add(logits + i * cb, src + (size_t)tgt[i] * cb * 4, (e - i) * cb * 4, "logits to host");
             i = e;
         }
-        HIPCHK(c, hipStreamSynchronize(c->stream), "sync");
-        return MTP_OK;
+        return out.wait();
     }
     std::vector<float> all((size_t)c->nar_rows * cb);
     HIPCHK(c, hipMemcpyAsync(all.data(), src, all.size() * 4, hipMemcpyDeviceToHost, c->stream), "logits to host");
