@@ -664,14 +664,20 @@ static hipError_t launch_pp(hipStream_t st, const bf16_t* X, int M, const bf16_t
 // CU), else 128 x 64 (fewer than 768 tiles here): a second round costs more
 // than the smaller tile saves (1075 x 4096 x 1024, 1088 tiles of 64 x 64, 21.2
 // us, 128 x 64 18.4; 700 x 4096 x 1024, 704 tiles of 64 x 64, 14.5 us, 128 x 64
-// 15.3; 128 x 128, one to two workgroups per CU, 21.2 and 17.5).  A split-K product of a long K with more than 256 tiles of 64
-// x 64 takes 128 x 64 and two splits (1075 x 1024 x 4096: 21.8 us; 64 x 64
-// 22.4 unsplit or split; at K = 1024 8.2 against 9.4 with 64 x 64 unsplit).
+// 15.3; 128 x 128, one to two workgroups per CU, 21.2 and 17.5).  A split-K
+// product of a long K with more than 256 tiles of 64 x 64 takes 128 x 64 and two
+// splits (1075 x 1024 x 4096: 21.8 us; 64 x 64 22.4 unsplit or split; at K =
+// 1024 8.2 against 9.4 with 64 x 64 unsplit), from K = 8192 on with more than
+// 192 (512 x 2048 x 8192, 256 tiles: 26.1 us in four splits, 64 x 64 29.1).
 //
 // The medium kernel for up to 192 rows (128 x 3072 x 1024: 6.0 us, 64 x 64
-// 9.0; 200 rows 8.8 against 8.0), and where its workgroups fit one round of
-// the CUs and a split-K product's K is short (325 x 1024 x 1024: 4.7 us
-// unsplit; 64 x 64 in two splits 5.3; at K = 4096 11.7 against 10.4 in four).
+// 9.0), and past them where its workgroups fit one round of the CUs (256 x 2048
+// x 512: 4.2 us, 64 x 64 6.2; 320 x 1536 x 512 4.7 against 6.2, 512 x 1024 x 256
+// 3.8 against 5.0; with more, 320 x 2048 x 512 6.5 against 6.1) and, with as
+// many K splits as the round has room for, the K of each is at most 3072 (with
+// the residual pass that follows: 325 x 1024 x 1024 unsplit 8.7 us, 64 x 64 in
+// two splits 9.6; 256 x 1024 x 4096 in two 10.8 against 11.4; 512 x 768 x 3072
+// unsplit 12.7 against 12.8; 320 x 1024 x 4096 unsplit 14.5 against 13.6).
 struct BigTile { int rows; int cols; };
 static int tile_count(int M, int N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 // The row count with the least rounds x (rows + 32) over `slots` workgroups.
@@ -690,10 +696,14 @@ static bool wide_tiles(int M, int N) { return M > 192 && tile_count(M, N, 128, 2
 static BigTile pick_tile(int M, int N, int K, bool splittable) {
     if (M <= 192) return {0, 0};
     if (wide_tiles(M, N)) return {best_rows(M, N, 256, cu_count(), 256), 256};
-    if (splittable && K < 2048 && med_groups(N) * ((M + 63) / 64) <= 256) return {0, 0};
+    const int wgs = med_groups(N) * ((M + 63) / 64);
+    int s = 1;
+    while (splittable && wgs * 2 * s <= 256) s *= 2;
+    if (wgs <= 256 && K / s <= 3072) return {0, 0};
     const int t64 = tile_count(M, N, 64, 64), slots = 3 * cu_count();
+    const int split_slots = K < 2048 ? slots : K < 8192 ? cu_count() : cu_count() * 3 / 4;
     // (64 k per stage; split-K products have K splits of whole stages, see gemm_splits)
-    if (K % 64 == 0 && t64 <= (splittable && K >= 2048 ? cu_count() : slots)) return {64, 64};
+    if (K % 64 == 0 && t64 <= (splittable ? split_slots : slots)) return {64, 64};
     return {128, 64};
 }
 template <class Epi>

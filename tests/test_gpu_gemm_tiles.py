@@ -22,7 +22,8 @@ ROWS = {
     33: "medium, 32 rows",
     65: "medium, 64 rows",
     192: "medium, 64 rows, the last full group",
-    193: "64 x 64 (one row in the last tile), 64 x 64, medium unsplit / 64 x 64 split",
+    193: "64 x 64 (one row in the last tile), 64 x 64, medium unsplit / in two splits",
+    257: "64 x 64, 64 x 64, medium unsplit / 64 x 64 split (one row in the last tile)",
     768: "64 x 64 in QKV and FFN1, the most workgroups of three per CU",
     1025: "128 x 64 (one row in the last tile), 128 x 64, 64 x 64 unsplit / 128 x 64 split",
     1536: "128 x 64, 128 (eight waves), 64 x 64 / 128 x 64",
@@ -37,7 +38,17 @@ ROWS = {
 
 @pytest.mark.parametrize("rows", list(ROWS))
 def test_every_row_of_a_tiled_product(rows):
-    shape = ModelShape(n_layers=2, d_model=1024, n_heads=16, d_ff=4096, k_heads=1, dtype="bf16", vocab=257, eos_id=256,
+    _check(rows, 1024)
+
+
+# d 512: QKV has 1536 columns, FFN1 2048; the last and the first rows past one round of the medium kernel
+@pytest.mark.parametrize("rows", [256, 257, 320, 321, 1024, 1025])
+def test_narrow_products_at_one_round_of_the_medium_kernel(rows):
+    _check(rows, 512)
+
+
+def _check(rows, d):
+    shape = ModelShape(n_layers=2, d_model=d, n_heads=d // 64, d_ff=4 * d, k_heads=1, dtype="bf16", vocab=257, eos_id=256,
                        n_phone=8, max_pos=160, nar=True)
     # utterances of 97 rows (odd starts in the tiles) and a rest
     n, rest = divmod(rows, 97)
