@@ -428,21 +428,23 @@ __global__ __launch_bounds__(QC_THREADS) void q_chunk_sort_kernel(QArgs a) {
     // (bounded by the tokens: the keys written must fit the chunk also when the offsets are not valid)
     const int64_t S0 = a.off[0], S1 = min(a.off[a.n_seqs], a.n_tokens);
     __syncthreads();
+    int64_t at_last = -1;                        // where the thread's last utterance ended
     for (int64_t i = (int64_t)max(a.w.c_first[c], 1u) + tid; i <= a.n_seqs; i += QC_THREADS) {
         const int64_t s = a.off[i - 1], e = a.off[i];
         const int64_t at = e - 1 - p0;
         if (e > s && at >= 0 && at < POS) atomicOr(&s_last[at >> 5], 1u << (at & 31));
         if (e > p0 + POS) break;                 // the later ones end later still
-        if (e == s) {
-            // an empty one: on to the last of the thread's that ends at the same
-            // place, by doubled and then halved steps (all between are empty too).
-            // One by one, a million empty utterances at one place took its chunk
-            // 630 us, and eight 5 ms.
+        if (e == at_last) {
+            // all since the thread's last one are empty: on to the last of its
+            // own that ends here, by doubled and then halved steps.  One by one,
+            // a million empty utterances at one place took their chunk 630 us,
+            // and eight 5 ms.
             int64_t k = QC_THREADS;
             for (; i + k <= a.n_seqs && a.off[i + k] == e; k *= 2) i += k;
             for (k /= 2; k >= QC_THREADS; k /= 2)
                 if (i + k <= a.n_seqs && a.off[i + k] == e) i += k;
         }
+        at_last = e;
     }
     __syncthreads();
     uint32_t key[GR * 4];
