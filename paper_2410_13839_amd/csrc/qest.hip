@@ -46,6 +46,7 @@
 #include <mutex>
 
 #include "../../include/mtp.h"
+#include "wave.h"
 
 namespace mtp {
 namespace {
@@ -62,14 +63,17 @@ constexpr int QC_THREADS = 512;                 // chunk workgroups
 constexpr int QC_GROUPS = 8;                    // 4-position groups per thread of a chunk
 constexpr int QC_POS = QC_GROUPS * 4 * QC_THREADS;   // positions of a chunk: a bucket's run in it is about 1 KB
 constexpr int QC_NB = 64;                       // buckets of the chunk path
+constexpr int QH_SLOTS = 256;                   // CUs: histogram workgroups resident at once (128 KB of LDS each)
+// whole slices of the chunk path: each one's partial row is 128 KB written and
+// read again (16 M tokens, one bucket: 221 slices 252 us, 256 264)
+constexpr int QH_SLICES = 220;
 constexpr int QC_END_WG = 1024;                 // q_ends workgroups
 
 struct QPlan {
     int V, NB, NWG, upw;        // vocab, buckets, range workgroups, utterances per range
-    int64_t S;                  // keys per slice
+    int64_t S;                  // keys per slice (chunk path: at least)
     int64_t max_slices;         // n_tokens / S + NB
     int nchunk;                 // chunks of the chunk path, 0: general path only
-    int64_t cS;                 // keys per slice of the chunk path (>= S)
 };
 
 struct QWs {
@@ -78,7 +82,7 @@ struct QWs {
     uint32_t* b_base;           // [NB + 1]
     uint32_t* s_base;           // [NB + 1] first slice of each bucket
     uint32_t* ctl;              // [0] 1 when the pairs exceed the key buffer; chunk path: [1] pairs with
-                                // a bad id, [2] 1 when the offsets are not valid
+                                // a bad id, [2] 1 when the offsets are not valid, [3] keys per slice
     uint16_t* keys;             // [n_tokens] low bits of the keys, by bucket, or by chunk and bucket
     uint32_t* c_cnt;            // [NB][nchunk] counts, then offsets within the bucket
     uint32_t* c_lb;             // [NB][nchunk] places of the buckets in a chunk
@@ -122,10 +126,6 @@ QPlan make_plan(int64_t n_tokens, int64_t n_seqs, int V) {
     // workspace keeps fitting it): at most 130 words a chunk of 32 KB.
     if (p.NB <= QC_NB && n_tokens >= (int64_t(1) << 23) && n_seqs < (int64_t(1) << 31))
         p.nchunk = (int)((n_tokens + QC_POS - 1) / QC_POS);
-    // one round of histogram workgroups (one per CU): 220 slices' worth of keys
-    // and the rests of 33 buckets
-    const int64_t cs = (n_tokens + 219) / 220;
-    p.cS = cs < p.S ? p.S : cs;
     return p;
 }
 
@@ -563,7 +563,33 @@ __global__ __launch_bounds__(QS_THREADS) void q_bucket_plan_kernel(QArgs a) {
     __shared__ uint32_t s_w[QS_THREADS / 64];
     const int NB = a.p.NB;
     const bool ch = chunked<CHUNKS>(a);
-    const int64_t S = ch ? a.p.cS : a.p.S;
+    int64_t S = a.p.S;
+    if constexpr (CHUNKS) {
+        // Chunk path: n / QH_SLICES keys per slice, or more where that many
+        // slices and a rest per bucket would not fit one round of histogram
+        // workgroups: of 16 lengths up to n / (QH_SLOTS - NB), which always
+        // fits, the smallest that does, a wave each.  105 M tokens: 44
+        // buckets (vocab 1200), 264 slices of n / 220 in two rounds 415 us in
+        // all, like this 355; 64 buckets, 256 slices either way, 360.
+        __shared__ uint32_t s_fit[QS_THREADS / 64];
+        const uint32_t n = (uint32_t)a.n_tokens;
+        const uint32_t lo = max((uint32_t)S, (n + QH_SLICES - 1) / QH_SLICES);
+        S = lo;
+        if (ch && NB > QH_SLOTS - QH_SLICES) {           // uniform
+            const uint32_t most = QH_SLOTS - NB, hi = max(lo, (n + most - 1) / most);
+            const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+            const uint32_t mine = lo + (uint32_t)((uint64_t)(hi - lo) * wave / (QS_THREADS / 64 - 1));
+            const uint32_t c = lane < NB ? a.w.b_cnt[lane] : 0u;
+            const float slices = wave_sum64((float)((c + mine - 1) / mine));   // (exact)
+            if (lane == 0) s_fit[wave] = slices <= (float)QH_SLOTS ? mine : hi;
+            __syncthreads();
+            uint32_t best = hi;
+            for (int w = 0; w < QS_THREADS / 64; ++w) best = min(best, s_fit[w]);
+            S = best;
+        }
+        if (ch && threadIdx.x == 0) a.w.ctl[3] = (uint32_t)S;
+        if (!ch) S = a.p.S;
+    }
     uint64_t carry = 0, scarry = 0;
     for (int b0 = 0; b0 < NB; b0 += QS_THREADS) {
         const int b = b0 + threadIdx.x;
@@ -683,7 +709,7 @@ __global__ __launch_bounds__(QH_THREADS) void q_slice_hist_kernel(QArgs a) {
     }
     const int b = lo;
     const bool ch = chunked<CHUNKS>(a);
-    const int64_t S = ch ? a.p.cS : a.p.S;
+    const int64_t S = ch ? a.w.ctl[3] : a.p.S;
     const uint4 z = {0u, 0u, 0u, 0u};
     for (uint32_t i = threadIdx.x; i < QB_BIN / 4; i += QH_THREADS) reinterpret_cast<uint4*>(hist)[i] = z;
     __syncthreads();

@@ -185,6 +185,9 @@ int main() {
             CHECK(bytes >= prev && bytes >= (uint64_t)n * 4);
             prev = bytes;
         }
+        for (int V = 1; V <= 8192; ++V)   // 1 .. 2048 buckets, on both sides of the chunk path's token count
+            for (int64_t n : {(int64_t)0, ((int64_t)1 << 23) - 1, (int64_t)1 << 23, (int64_t)105 << 20})
+                CHECK(mtp_q_workspace_size(n, 1 + n / 297, V, &bytes) == MTP_OK && bytes >= (uint64_t)n * 4);
         CHECK(mtp_q_workspace_size(-1, 0, 1025, &bytes) == MTP_EINVAL);
         CHECK(mtp_q_workspace_size(10, 1, 0, &bytes) == MTP_EINVAL);
         CHECK(mtp_q_workspace_size(10, 1, 9000, &bytes) == MTP_EINVAL);
