@@ -37,13 +37,12 @@ namespace mtp {
 // scalar so the step guards are uniform branches.
 constexpr int GM_NW = 16;
 
-template <int MT, int NT, int MAXST, int XP, class Epi>
-__global__ __launch_bounds__(64 * GM_NW) void gemm_med_bf16(const bf16_t* __restrict__ X, int ldx, int M,
+template <int MT, int NT, int MAXST, class Epi>
+__global__ __launch_bounds__(64 * GM_NW) void gemm_med_bf16(const bf16_t* __restrict__ X, int M,
                                                             const bf16_t* __restrict__ W, int N, int K,
                                                             int k_per_split, Epi epi) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r = lane & 15, g = lane >> 4;
     const int ntiles = (N + 15) >> 4;
     const int nt0 = blockIdx.x * NT;
     const int m0 = blockIdx.y * 16 * MT;
@@ -54,18 +53,12 @@ __global__ __launch_bounds__(64 * GM_NW) void gemm_med_bf16(const bf16_t* __rest
 #pragma unroll
     for (int j = 0; j < NT; ++j)
         wp[j] = W + ((size_t)min(nt0 + j, ntiles - 1) * (K >> 5) + (kb >> 5)) * 512 + lane * 8;
-    // XP: X in fragment order (one contiguous 1 KB block per row tile and k
-    // step, rows padded to 16), else row-major
+    // X in fragment order: one contiguous 1 KB block per row tile and k step, rows padded to 16
     const bf16_t* xp[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        if (XP) {
-            const int t = min(m0 / 16 + mt, (M - 1) >> 4);
-            xp[mt] = X + ((size_t)t * (K >> 5) + (kb >> 5)) * 512 + lane * 8;
-        } else {
-            const int m = min(m0 + 16 * mt + r, M - 1);
-            xp[mt] = X + (size_t)m * ldx + kb + g * 8;
-        }
+        const int t = min(m0 / 16 + mt, (M - 1) >> 4);
+        xp[mt] = X + ((size_t)t * (K >> 5) + (kb >> 5)) * 512 + lane * 8;
     }
     f32x4_t acc[NT][MT];
 #pragma unroll
@@ -83,8 +76,7 @@ __global__ __launch_bounds__(64 * GM_NW) void gemm_med_bf16(const bf16_t* __rest
 #pragma unroll
                 for (int j = 0; j < NT; ++j) wv[u][j] = *reinterpret_cast<const uint4*>(wp[j] + (size_t)ss * 512);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    xv[u][mt] = *reinterpret_cast<const uint4*>(xp[mt] + (XP ? (size_t)ss * 512 : (size_t)ss * 32));
+                for (int mt = 0; mt < MT; ++mt) xv[u][mt] = *reinterpret_cast<const uint4*>(xp[mt] + (size_t)ss * 512);
             }
         }
 #pragma unroll
@@ -154,9 +146,8 @@ static int med_rows(int M, int N, bool splittable) {
     return mt;
 }
 
-template <int MT, int XP, class Epi>
-static void launch_med(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K, int splits,
-                       Epi epi) {
+template <int MT, class Epi>
+static void launch_med(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, int N, int K, int splits, Epi epi) {
     constexpr int NT = GM_NT;
     static_assert(NT * MT <= 8, "LDS reduction");
     const int kps = K / splits;
@@ -166,20 +157,13 @@ static void launch_med(hipStream_t st, const bf16_t* X, int ldx, int M, const bf
     // one round of loads holds at most MAXST x (NT + MT) fragments per wave
     constexpr int CAP = NT * MT >= 8 ? 2 : 4;
     if (per_wave <= 1)
-        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 1, XP, Epi>), grid, block, 0, st, X, ldx, M, W, N, K, kps, epi);
+        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 1, Epi>), grid, block, 0, st, X, M, W, N, K, kps, epi);
     else if (per_wave == 2 || CAP == 2)
-        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 2, XP, Epi>), grid, block, 0, st, X, ldx, M, W, N, K, kps, epi);
+        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 2, Epi>), grid, block, 0, st, X, M, W, N, K, kps, epi);
     else if (per_wave == 3)
-        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 3, XP, Epi>), grid, block, 0, st, X, ldx, M, W, N, K, kps, epi);
+        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, 3, Epi>), grid, block, 0, st, X, M, W, N, K, kps, epi);
     else
-        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, CAP, XP, Epi>), grid, block, 0, st, X, ldx, M, W, N, K, kps, epi);
-}
-
-template <int MT, class Epi>
-static void launch_med_x(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K, int splits,
-                         int xpk, Epi epi) {
-    if (xpk) launch_med<MT, 1>(st, X, ldx, M, W, N, K, splits, epi);
-    else launch_med<MT, 0>(st, X, ldx, M, W, N, K, splits, epi);
+        hipLaunchKernelGGL((gemm_med_bf16<MT, NT, CAP, Epi>), grid, block, 0, st, X, M, W, N, K, kps, epi);
 }
 
 // ---------------------------------------------------------------- large bf16
@@ -703,17 +687,20 @@ static BigTile pick_tile(int M, int N, int K, bool splittable) {
     const int t64 = tile_count(M, N, 64, 64), slots = 3 * cu_count();
     const int split_slots = K < 2048 ? slots : K < 8192 ? cu_count() : cu_count() * 3 / 4;
     // (64 k per stage; split-K products have K splits of whole stages, see gemm_splits)
-    if (K % 64 == 0 && t64 <= (splittable ? split_slots : slots)) return {64, 64};
+    if (t64 <= (splittable ? split_slots : slots)) return {64, 64};
     return {128, 64};
 }
 template <class Epi>
-static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, const bf16_t* W, int N, int K,
-                              int splits, int xpk, Epi epi) {
+static hipError_t launch_bf16(hipStream_t st, const GemmArgs& a, int splits, Epi epi) {
     constexpr bool split = std::is_same<Epi, EpiPartial>::value;
-    if (splits < 1 || K % (32 * splits)) return hipErrorInvalidValue;
+    const bf16_t* X = (const bf16_t*)a.X;
+    const bf16_t* W = (const bf16_t*)a.W;
+    const int M = a.M, N = a.N, K = a.K;
+    // activations in fragment order; K is a model width, a multiple of 256
+    if (!a.xpk || K % 64 || splits < 1 || K % (32 * splits)) return hipErrorInvalidValue;
     if constexpr (std::is_same<Epi, EpiResid>::value) {
         // (the residual epilogue's operands leave no registers for 256 rows)
-        if (!xpk || !gemm_resid_in_place(M, N)) return hipErrorInvalidValue;
+        if (!gemm_resid_in_place(M, N)) return hipErrorInvalidValue;
         switch (wide_tiles(M, N) ? best_rows(M, N, 128, 2 * cu_count(), 224) : 128) {
         case 128: return launch_duo<4, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
         case 160: return launch_duo<5, 4, 1, 4, 2>(st, X, M, W, N, K, splits, false, epi);
@@ -725,16 +712,14 @@ static hipError_t launch_bf16(hipStream_t st, const bf16_t* X, int ldx, int M, c
         const bool mfast = M <= N;
         if (bt.rows == 0) {
             switch (med_rows(M, N, split)) {
-            case 1: launch_med_x<1>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
-            case 2: launch_med_x<2>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
-            default: launch_med_x<4>(st, X, ldx, M, W, N, K, splits, xpk, epi); break;
+            case 1: launch_med<1>(st, X, M, W, N, K, splits, epi); break;
+            case 2: launch_med<2>(st, X, M, W, N, K, splits, epi); break;
+            default: launch_med<4>(st, X, M, W, N, K, splits, epi); break;
             }
             return hipGetLastError();
         }
-        if (!xpk) return hipErrorInvalidValue;   // large products take fragment-order activations only
         if (bt.cols == 64) {
-            if (bt.rows == 64 && K % (64 * splits) == 0)
-                return launch_duo<2, 2, 2, 3, 3>(st, X, M, W, N, K, splits, mfast, epi);
+            if (bt.rows == 64) return launch_duo<2, 2, 2, 3, 3>(st, X, M, W, N, K, splits, mfast, epi);
             return launch_duo<4, 2, 1, 4, 3>(st, X, M, W, N, K, splits, mfast, epi);
         }
         switch (bt.rows) {
@@ -780,23 +765,15 @@ int gemm_splits(int M, int N, int K, int most) {
 
 hipError_t gemm(hipStream_t st, const GemmArgs& a) {
     if (a.dtype != 1) return gemm_f32(st, a);
-    const bf16_t* X = (const bf16_t*)a.X;
-    const bf16_t* W = (const bf16_t*)a.W;
     switch (a.epi) {
-    case EPI_QKV:
-        return launch_bf16(st, X, a.ldx, a.M, W, a.N, a.K, 1, a.xpk, EpiQKV<bf16_t>{a.q, a.bias, a.rows, a.kv, a.d});
-    case EPI_GELU:
-        return launch_bf16(st, X, a.ldx, a.M, W, a.N, a.K, 1, a.xpk,
-                           EpiGelu<bf16_t>{(bf16_t*)a.out, a.bias, a.ldo, a.opk});
-    case EPI_PARTIAL:
-        return launch_bf16(st, X, a.ldx, a.M, W, a.N, a.K, a.splits, a.xpk,
-                           EpiPartial{(float*)a.out, a.ldo, a.split_stride});
+    case EPI_QKV: return launch_bf16(st, a, 1, EpiQKV<bf16_t>{a.q, a.bias, a.rows, a.kv, a.d});
+    case EPI_GELU: return launch_bf16(st, a, 1, EpiGelu<bf16_t>{(bf16_t*)a.out, a.bias, a.ldo, a.opk});
+    case EPI_PARTIAL: return launch_bf16(st, a, a.splits, EpiPartial{(float*)a.out, a.ldo, a.split_stride});
     case EPI_RESID:
         // large-M bf16 products only, no K split
         if (a.splits != 1 || !gemm_resid_in_place(a.M, a.N) || a.N % 4) return hipErrorInvalidValue;
-        return launch_bf16(st, X, a.ldx, a.M, W, a.N, a.K, 1, a.xpk, EpiResid{(float*)a.out, a.bias, a.ldo});
-    case EPI_LOGITS:
-        return launch_bf16(st, X, a.ldx, a.M, W, a.N, a.K, 1, a.xpk, EpiLogits{(float*)a.out, a.bias, a.ldo, a.N});
+        return launch_bf16(st, a, 1, EpiResid{(float*)a.out, a.bias, a.ldo});
+    case EPI_LOGITS: return launch_bf16(st, a, 1, EpiLogits{(float*)a.out, a.bias, a.ldo, a.N});
     }
     return hipErrorInvalidValue;
 }

@@ -16,7 +16,7 @@ struct GemmArgs {
     const void* X; int ldx; int M;
     const void* W; int N; int K;
     int splits;           // split-K factor (EPI_PARTIAL only)
-    int xpk;              // bf16 X in MFMA fragment order (frag_off)
+    int xpk;              // 1: bf16 X in MFMA fragment order (frag_off), the only order these products take
     int opk;              // EPI_GELU: bf16 output in fragment order
     // epilogue operands
     const float* bias;
