@@ -341,9 +341,8 @@ hipError_t attention_mfma(hipStream_t st, const AttnMfmaArgs& a) {
         if (nw == 8) return attn_dec_go<8>(st, a);
         return attn_dec_go<4>(st, a);
     }
-    // prefill: tiles of at most a.qt rows (16, 32 or 64), one split
-    if (a.n_splits != 1) return hipErrorInvalidValue;
-    if (a.qt != 64) return hipErrorInvalidValue;
+    // prefill: tiles of at most 64 rows, one split
+    if (a.n_splits != 1 || a.qt != MTP_PREFILL_ROWS) return hipErrorInvalidValue;
     // dynamic LDS: one page number per page of a sequence
     const size_t lds = (size_t)a.kv.max_pages_per_seq * sizeof(int);
     if (lds > 48 * 1024) return hipErrorInvalidValue;

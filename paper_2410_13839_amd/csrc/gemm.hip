@@ -6,14 +6,14 @@
 // that receives 4 consecutive n of one row m.
 //
 //  * gemm_med_bf16: M <= 192 (decode rows of the batched path, the heads),
-//    and products too small for 96 tiles of 64 x 64.
+//    and more rows while its workgroups fit one round of the CUs (pick_tile).
 //    A weight stream (M = 128 rows is ~128 flop per weight byte, below the
 //    MFMA / HBM ridge), so W fragments go straight from HBM into MFMA
 //    registers (no LDS round trip), 16 waves per workgroup split the K range,
 //    each wave loading its own activation fragments from L2 (no LDS staging:
 //    no two waves read the same k), and one LDS reduction over the waves
 //    precedes the epilogue.  The grid is sized so every CU streams.
-//  * gemm_pp_bf16, gemm_duo_bf16: M > 192 (prefill, NAR).  Large tiles on
+//  * gemm_pp_bf16, gemm_duo_bf16: the other products (prefill, NAR).  Tiles on
 //    MFMA with both operands streamed global -> LDS in fragment order.
 // The fp32 model's products are in f32.hip.
 #include <algorithm>
@@ -167,8 +167,7 @@ static void launch_med(hipStream_t st, const bf16_t* X, int M, const bf16_t* W, 
 }
 
 // ---------------------------------------------------------------- large bf16
-// Prefill, NAR (M > 192) products: tiles of BM rows x
-// BN columns, 16 x 16 x 32 MFMA.  Both operands are in fragment order
+// Products of more than 192 rows (prefill, NAR): tiles of BM rows x BN columns, 16 x 16 x 32 MFMA.  Both operands are in fragment order
 // (activations written so by their producers, weights packed at load), so a
 // 16 x 32 fragment is one contiguous 1 KB; it travels global -> LDS by one
 // global_load_lds_dwordx4 per wave (lane l's 16 bytes land at byte 16 l, the
@@ -457,8 +456,9 @@ __global__ __launch_bounds__(256, WGS) void gemm_duo_bf16(const bf16_t* __restri
     }
 }
 
-// M > 256, eight waves, tiles of BM = 32 WFM rows x 256 columns (WFM = 4 .. 8,
-// so that a product's tiles fill whole rounds of the CUs; see pick_tile).
+// At least 192 tiles of 128 x 256 (wide_tiles): eight waves, tiles of BM = 32
+// WFM rows x 256 columns (WFM = 4 .. 8, so that a product's tiles fill whole
+// rounds of the CUs; see pick_tile).
 //
 // What bounds a tile of this size is LDS bandwidth against the matrix cores:
 // a 32-k step of 256 x 256 reads 96 KB of operands from LDS and lets 32 KB of
@@ -749,8 +749,8 @@ int gemm_resid_in_place(int M, int N) {
 // (325 x 1024 x 1024, 192 workgroups: 4.7 us unsplit, 6.5 in two; 32 x 1024 x
 // 1024 2.8 in four, 3.0 in eight; 32 x 1536 x 6144, 48 workgroups: 6.7 in four,
 // 6.9 in eight).  Tiles: up to two workgroups per CU, each split at least 512 k
-// (325 x 1024 x 4096, 96 tiles: 10.4 us in four, 10.8 in eight; 512 x 1024 x
-// 1024, 128 tiles: 5.4 in two, 5.5 in four).  The residual pass that follows
+// (325 x 1024 x 4096, 96 tiles: 10.4 us in four, 10.8 in eight; 576 x 1024 x
+// 1024, 144 tiles: 6.6 in two, 7.2 in four).  The residual pass that follows
 // reads every split.
 int gemm_splits(int M, int N, int K, int most) {
     const BigTile bt = pick_tile(M, N, K, true);

@@ -72,7 +72,7 @@ hipError_t attention_decode(hipStream_t st, const AttnDecArgs& a);
 hipError_t attention_decode_merge(hipStream_t st, const AttnDecArgs& a);
 
 // MFMA attention for bf16 caches: mode 0 = decode (one tile per sequence, rows
-// from the sequence state), mode 1 = prefill (tiles of up to 16 rows).
+// from the sequence state), mode 1 = prefill (tiles of up to 64 rows).
 // Hand-off state of the fused decode front (qkv_front): one flag per QKV
 // column tile, set by the tile once its columns are stored.  Consecutive
 // launches use different flag sets: a launch clears the set of the next one
