@@ -336,7 +336,7 @@ int mtp_get_tokens(mtp_ctx* ctx, int32_t* tokens);
 #define MTP_KCLASS_HEADS       5   /* final LN -> K head projections          */
 #define MTP_KCLASS_GEMM_OPROJ  6   /* attention out x W_o^T (residual part.)  */
 #define MTP_KCLASS_SELECT      7   /* top_k, Viterbi lattice and accept       */
-#define MTP_KCLASS_RESID_LN    8   /* residual + LayerNorm rows (batched path, two per layer) */
+#define MTP_KCLASS_RESID_LN    8   /* residual + LayerNorm rows (more than 16 rows, two per layer) */
 #define MTP_KCLASS_QKV_ATTN    9   /* LN1 -> x W_qkv^T, K/V into the cache, attention over the
                                       cached keys, in one launch (B * K <= 8 rows, d <= 1024) */
 #define MTP_KCLASS_QKV_FRONT  10   /* LN1 -> x W_qkv^T, K/V into the cache, then the decode

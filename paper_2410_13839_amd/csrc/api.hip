@@ -1389,7 +1389,8 @@ int mtp_nar_get_logits(mtp_ctx* c, int stage, float* logits) {
     // The target rows are one run of rows per utterance: copied run by run
     // straight to the caller where a run is worth a copy of its own (64 KB);
     // otherwise all rows through a buffer (8 utterances, 6720 rows of which 4200
-    // are targets: the whole call 32.5 ms through the buffer, 27.4 run by run).
+    // are targets: the whole NAR pass 29.7 ms through the buffer, 28.0 run by
+    // run; one utterance, 750 of 1075 rows, 9.6 and 9.45).
     const std::vector<int32_t>& tgt = c->h_tgt;
     size_t runs = 0;
     for (size_t i = 0; i < tgt.size(); ++i) runs += i == 0 || tgt[i] != tgt[i - 1] + 1;
